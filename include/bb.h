@@ -288,7 +288,11 @@ int bb_layernorm_matmul_unfused(const void* X, const void* gamma,
  * the operand of the second product; output sums and row sums in fp32, the
  * quotient rounded to bf16 once.  Errors as for the other operators.
  *
- * Few queries (decoding: fewer (problem, 128-query block) pairs than half the
+ * Few queries (2 .. 32 per problem, any N): a streaming kernel reads K and V
+ * once, straight into matrix-instruction operands; from 1024 keys on several
+ * workgroups share a problem's keys, and their significand-exponent pairs are
+ * added as below by the problem's last workgroup or by a second kernel.
+ * More queries but few pairs (fewer (problem, 128-query block) pairs than half the
  * compute units, and at least 8 blocks of 64 keys): the loop over the key
  * blocks is cut into equal ranges that run in parallel workgroups (Rule 3's
  * parallel form); each stores its unnormalised output and row sum with their

@@ -29,6 +29,7 @@ constexpr int64_t kStreamTMaxM = 16;  // rows the weight-streaming kernel for tr
 constexpr int64_t kPrescaleFloorM = 16; // up to this many rows no room is planned for BB_VARIANT_PRESCALE's gain-scaled copy of X
 constexpr int64_t kNestAutoMaxD = 256, kNestAutoMaxF = 768, kNestAutoMaxM = 16 * 256;   // shapes on which AUTO runs the fully fused nest
 constexpr int64_t kPrescaleMinM = 256; // rows from which AUTO runs the statistics loop as a kernel of its own
+constexpr int64_t kGroupOwnSlots = 128;  // partial results of one problem that its last workgroup adds itself
 constexpr size_t kAlign = 256;
 
 std::mutex g_mu;
@@ -366,6 +367,20 @@ int attn_decode_plan(int64_t B, int64_t N, int cus, int64_t* nsplit) {
     const int64_t nblocks = (N + ATTN_BK - 1) / ATTN_BK, units = B * ((nblocks + 3) / 4);
     const int64_t per = std::min<int64_t>(std::max<int64_t>((units + 3 * cus - 1) / (3 * (int64_t)cus), 1), 64);
     *nsplit = (nblocks + 4 * per - 1) / (4 * per);
+    return (int)per;
+}
+
+// A few queries per problem: blocks per wavefront of attention_group_kernel and workgroups per problem.  About two
+// workgroups per compute unit (128 problems x 8 queries x 5000 keys of 64 features: 30.6 us, with three or four
+// 33.7 and 34.3); sequences below 1024 keys are not split (a workgroup has at most eight steps, adding the
+// pairs of several workgroups costs as much as it saves).
+int attn_group_plan(int64_t B, int64_t N, int64_t d, int64_t dv, int cus, int64_t* nsplit) {
+    const int64_t nblocks = (N + attn_group_keys((int)d, (int)dv) - 1) / attn_group_keys((int)d, (int)dv);
+    const int64_t groups = (nblocks + 3) / 4;
+    int64_t per = groups;
+    if (N >= 1024) per = std::max<int64_t>((B * groups + 2 * cus - 1) / (2 * (int64_t)cus), 1);
+    per = std::min(per, groups);
+    *nsplit = (groups + per - 1) / per;
     return (int)per;
 }
 
@@ -1046,34 +1061,52 @@ int bb_attention(const void* Q, const void* K, const void* V, void* O, int64_t B
     a.B = (int)B;
     a.M = (int)M;
     a.N = (int)N;
-    if (M == 1) {
-        // one query per problem: the streaming kernel (no matrix product), any N
+    if (M <= ATTN_GROUP_MAXM) {
+        // one query per problem: the streaming kernel without matrix products; a few: the one with (any N)
+        const bool one = M == 1;
+        const int cus = std::min(dev->cus, kPlanCUs);
         int64_t nsplit = 1;
-        a.nt_split = attn_decode_plan(B, N, std::min(dev->cus, kPlanCUs), &nsplit);
+        a.nt_split = one ? attn_decode_plan(B, N, cus, &nsplit) : attn_group_plan(B, N, d, dv, cus, &nsplit);
         if (B * nsplit > 0x7fffffffLL) return BB_ERR_SHAPE;
         a.nsplit = (int)nsplit;
         a.tiles_q = 1;
         a.wgs_per_xcd = 0;
         a.c = (float)(1.4426950408889634 / std::sqrt((double)d));
-        const size_t zone = attn_zone_bytes(B), pbytes = align_up((size_t)B * nsplit * dv * 4);
-        if (int rc = ensure_workspace(zone + pbytes + align_up((size_t)B * nsplit * 8))) return rc;
-        const size_t had = g_ws.attn_zone;
-        mark_dirty(0);
-        if (had < zone) {                  // counters: zero before their first use; every launch leaves them zero
-            if (int rc = fill_zero(g_ws.ptr, zone, st)) return rc;
-            g_ws.attn_zone = zone;
-        } else {
-            g_ws.attn_zone = had;
+        a.cnt = nullptr;
+        a.part = nullptr;
+        a.ml = nullptr;
+        if (one || nsplit > 1) {
+            const size_t zone = attn_zone_bytes(B), pbytes = align_up((size_t)B * M * nsplit * dv * 4);
+            if (int rc = ensure_workspace(zone + pbytes + align_up((size_t)B * M * nsplit * 8))) return rc;
+            const size_t had = g_ws.attn_zone;
+            mark_dirty(0);
+            if (had < zone) {              // counters: zero before their first use; every launch leaves them zero
+                if (int rc = fill_zero(g_ws.ptr, zone, st)) return rc;
+                g_ws.attn_zone = zone;
+            } else {
+                g_ws.attn_zone = had;
+            }
+            a.cnt = (unsigned*)g_ws.ptr;
+            a.part = (float*)((char*)g_ws.ptr + zone);
+            a.ml = (float*)((char*)g_ws.ptr + zone + pbytes);
+            // (the last workgroup of a problem adds few slots faster than a second launch starts, 10.7 against 11.4 us
+            // for 4 queries x 16 slots, many slower, 14.5 against 12.1 for 8 x 32 and 45 against 13 for 16 x 64)
+            if (!one && M * nsplit > kGroupOwnSlots) a.cnt = nullptr;
         }
-        a.cnt = (unsigned*)g_ws.ptr;
-        a.part = (float*)((char*)g_ws.ptr + zone);
-        a.ml = (float*)((char*)g_ws.ptr + zone + pbytes);
-        const dim3 grid((unsigned)(B * nsplit)), block(256);
+        const dim3 grid((unsigned)(B * nsplit));
+        const int mt = M <= 16 ? 1 : 2;
         prof_begin(st);
-        if (d == 64 && dv == 64) attn_decode_launch<64, 64>(grid, st, a);
-        else if (d == 64) attn_decode_launch<64, 128>(grid, st, a);
-        else if (dv == 64) attn_decode_launch<128, 64>(grid, st, a);
-        else attn_decode_launch<128, 128>(grid, st, a);
+        auto launch = [&](auto DKC, auto DVC) {
+            constexpr int DK = decltype(DKC)::value, DV = decltype(DVC)::value;
+            if (one) attn_decode_launch<DK, DV>(grid, st, a);
+            else attn_group_launch<DK, DV>(mt, grid, st, a);
+        };
+        using H64 = std::integral_constant<int, 64>;
+        using H128 = std::integral_constant<int, 128>;
+        if (d == 64 && dv == 64) launch(H64(), H64());
+        else if (d == 64) launch(H64(), H128());
+        else if (dv == 64) launch(H128(), H64());
+        else launch(H128(), H128());
         BB_HIP(hipGetLastError());
         prof_mark("attention", st);
         return BB_OK;
@@ -1122,10 +1155,12 @@ int bb_attention(const void* Q, const void* K, const void* V, void* O, int64_t B
 size_t bb_attention_workspace_bytes(int64_t B, int64_t M, int64_t N, int64_t d, int64_t dv) {
     if (B < 0 || M < 0 || N < 1 || (d != 64 && d != 128) || (dv != 64 && dv != 128)) return 0;
     if (B == 0 || M == 0) return 0;
-    if (M == 1) {
+    if (M <= ATTN_GROUP_MAXM) {
         int64_t nsplit = 1;
-        attn_decode_plan(B, N, kPlanCUs, &nsplit);
-        return attn_zone_bytes(B) + align_up((size_t)B * nsplit * dv * 4) + align_up((size_t)B * nsplit * 8);
+        if (M == 1) attn_decode_plan(B, N, kPlanCUs, &nsplit);
+        else attn_group_plan(B, N, d, dv, kPlanCUs, &nsplit);
+        if (M > 1 && nsplit == 1) return 0;
+        return attn_zone_bytes(B) + align_up((size_t)B * M * nsplit * dv * 4) + align_up((size_t)B * M * nsplit * 8);
     }
     const int s = attn_key_splits(B * ((M + 127) / 128), (N + ATTN_BK - 1) / ATTN_BK, kPlanCUs);
     if (s < 2) return 0;

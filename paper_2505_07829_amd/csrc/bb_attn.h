@@ -51,13 +51,17 @@ struct AttnArgs {
     int nsplit, nt_split;
     float* part;        // [B M][nsplit][DV]
     float* ml;          // [B M][nsplit][2]
-    // attention_decode_kernel: arrival counters, one per problem, zero between launches (the last
-    // workgroup of a problem to arrive adds the problem's partial results)
+    // attention_decode_kernel, attention_group_kernel: arrival counters, one per problem, zero between launches
+    // (the last workgroup of a problem to arrive adds the problem's partial results); attention_group_kernel: null =
+    // one workgroup per problem, or the combine kernel adds them
     unsigned* cnt;
 };
 
 // a workgroup has NW = 4 or 8 wavefronts of 32 queries each
 constexpr int ATTN_BK = 64;       // keys per step
+constexpr int ATTN_GROUP_MAXM = 32;   // queries per problem that attention_group_kernel takes (two groups of 16)
+// keys per step of a wavefront of attention_group_kernel
+constexpr int attn_group_keys(int dk, int dv) { return dk == 64 && dv == 64 ? 64 : 32; }
 constexpr float ATTN_SLACK = 8.f; // log2 of the largest significand a row keeps before its exponent moves
 
 // chunk position of (row, chunk) in an LDS tile with CPR 16-byte chunks per row,
@@ -622,6 +626,202 @@ __global__ __launch_bounds__(256) void attention_decode_kernel(const AttnArgs p)
     if (last_arrival == 0u || w != 0) return;
     attention_combine_row<DV>(p.part, p.ml, p.O, (size_t)b, p.nsplit, p.c, lane);
     if (lane == 0) __hip_atomic_store(p.cnt + b, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+// A few queries per problem (2 .. 16 MT: grouped-query and speculative decoding, short chunks): like the
+// one-query kernel a stream over K and V, but with matrix products.  Nothing is staged through LDS: a wavefront
+// takes blocks of 32 NSUB keys, and every load lands in the registers that a 16x16x32 matrix instruction
+// takes it from.
+//   Scores S^T = K Q^T: a lane holds 8 features of one key row (16 rows x 64 bytes per load instruction, the 2 or 4
+// instructions of a row group issued together), so the result has one query per lane (lane % 16) and
+// keys 16 t + 4 (lane / 16) + v of the block.
+//   Output O^T = V^T P^T: those eight scores of a lane are its eight contraction slots of the second product, without
+// any exchange, if V^T's slot j of lane group g is key 4 g + j (j < 4) or 16 + 4 g + j - 4.  V rows are loaded
+// in that order (whole rows per instruction) and turned in registers (transpose8x8).
+// Softmax as in the tiled kernel (running row exponent that moves by more than 2^ATTN_SLACK, P rounded to bf16);
+// the wavefronts' and the workgroups' pairs are added as in attention_decode_kernel.
+//   What bounds it: the bytes of K and V in flight.  A block is 16 KiB per wavefront, all of it requested at
+// once, and no wavefront waits for another before its last block.  K goes through the caches (an instruction
+// takes 64 bytes of each row, the next ones the rest of the line), V, whose rows are taken whole, is non-temporal:
+// 64 problems x 8 queries x 5000 keys of 64 features 18.5 us against 20.6 with both non-temporal and 20.0 with
+// both cached, 59.7 in the tiled kernel (120 of whose 128 query rows are padding there, and whose keys split only into
+// equal ranges); 256 x 8 x 4096 of 128 features 86 against 97 us (6.2 TB/s).  Requesting the next block's K before the
+// exponentials was slower (23.1 us: the registers cost the third wavefront per SIMD).
+template <int DK, int DV, int MT>
+__global__ __launch_bounds__(256, 2) void attention_group_kernel(const AttnArgs p) {
+    constexpr int NSUB = DK == 64 && DV == 64 ? 2 : 1;       // 32-key subblocks per step
+    constexpr int KB = 32 * NSUB;
+    static_assert(KB == attn_group_keys(DK, DV), "the launch plan counts blocks of this size");
+    constexpr int NKS = DK / 32;                             // contraction slices of the first product
+    constexpr int CW = DV / 16;                              // consecutive value columns per lane
+    typedef __attribute__((__vector_size__(CW / 2 * sizeof(u32)))) u32 vrow_t;
+    __shared__ float s_o[4][16 * MT][DV];
+    __shared__ float s_ml[4][16 * MT][2];
+    __shared__ unsigned last_arrival;
+    const int lane = threadIdx.x & 63, l16 = lane & 15, g = lane >> 4;
+    const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int b = blockIdx.x / p.nsplit, split = blockIdx.x % p.nsplit;
+    const u16* const Kb = p.K + (size_t)b * p.N * DK + 8 * g;
+    const u16* const Vb = p.V + (size_t)b * p.N * DV + CW * l16;
+
+    Chunk qf[MT][NKS];                                       // query 16 mt + l16, features 32 ks + 8 g ..
+#pragma unroll
+    for (int mt = 0; mt < MT; ++mt) {
+        const int q = min(16 * mt + l16, p.M - 1);           // (rows past the end are computed and not stored)
+#pragma unroll
+        for (int ks = 0; ks < NKS; ++ks) qf[mt][ks].u = ldg16(p.Q + ((size_t)b * p.M + q) * DK + 32 * ks + 8 * g);
+    }
+    f32x4 acc[MT][CW];                                       // [c][v]: value column CW (4 g + v) + c of query l16
+    float m_run[MT], l_run[MT];
+#pragma unroll
+    for (int mt = 0; mt < MT; ++mt) {
+        m_run[mt] = -INFINITY;
+        l_run[mt] = 0.f;
+#pragma unroll
+        for (int c = 0; c < CW; ++c) acc[mt][c] = f32x4{0.f, 0.f, 0.f, 0.f};
+    }
+
+    const int kstep = 4 * KB, kfirst = (split * p.nt_split * 4 + w) * KB, kend = min(p.N, kfirst + p.nt_split * kstep);
+    for (int key0 = kfirst; key0 < kend; key0 += kstep) {    // (the same trips for the whole wavefront)
+        Chunk kf[NSUB][2][NKS];
+        vrow_t vr[NSUB][8];
+        // (rows past the end of the sequence: the last row, its scores are masked)
+#pragma unroll
+        for (int u = 0; u < NSUB; ++u)
+#pragma unroll
+            for (int t = 0; t < 2; ++t) {
+                const size_t row = (size_t)min(key0 + 32 * u + 16 * t + l16, p.N - 1) * DK;
+#pragma unroll
+                for (int ks = 0; ks < NKS; ++ks) kf[u][t][ks].u = ldg16(Kb + row + 32 * ks);
+            }
+#pragma unroll
+        for (int u = 0; u < NSUB; ++u)
+#pragma unroll
+            for (int e = 0; e < 8; ++e) {
+                const int row = min(key0 + 32 * u + 16 * (e >> 2) + 4 * g + (e & 3), p.N - 1);
+                vr[u][e] = __builtin_nontemporal_load(reinterpret_cast<const vrow_t*>(Vb + (size_t)row * DV));
+            }
+        f32x4 scs[MT][NSUB][2];
+#pragma unroll
+        for (int mt = 0; mt < MT; ++mt)
+#pragma unroll
+            for (int u = 0; u < NSUB; ++u)
+#pragma unroll
+                for (int t = 0; t < 2; ++t) {
+                    scs[mt][u][t] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+                    for (int ks = 0; ks < NKS; ++ks)
+                        scs[mt][u][t] =
+                            __builtin_amdgcn_mfma_f32_16x16x32_bf16(kf[u][t][ks].v, qf[mt][ks].v, scs[mt][u][t], 0, 0, 0);
+                }
+        Chunk pb[MT][NSUB];
+#pragma unroll
+        for (int mt = 0; mt < MT; ++mt) {
+            f32x4 (&sc)[NSUB][2] = scs[mt];
+            float mx = -INFINITY;
+#pragma unroll
+            for (int u = 0; u < NSUB; ++u)
+#pragma unroll
+                for (int t = 0; t < 2; ++t)
+#pragma unroll
+                    for (int v = 0; v < 4; ++v) {
+                        if (key0 + 32 * u + 16 * t + 4 * g + v >= p.N) sc[u][t][v] = -INFINITY;   // keys past the end take no part
+                        mx = fmaxf(mx, sc[u][t][v]);
+                    }
+            mx = fmaxf(mx, __shfl_xor(mx, 16));
+            mx = fmaxf(mx, __shfl_xor(mx, 32));              // finite: key0 < N
+            const bool moves = mx * p.c > m_run[mt] * p.c + ATTN_SLACK;
+            if (__builtin_amdgcn_ballot_w64(moves) != 0) {
+                const float m_new = moves ? mx : m_run[mt];
+                const float alpha = __builtin_amdgcn_exp2f((m_run[mt] - m_new) * p.c);   // 1 where the row stays
+                l_run[mt] *= alpha;
+#pragma unroll
+                for (int c = 0; c < CW; ++c) acc[mt][c] *= alpha;
+                m_run[mt] = m_new;
+            }
+            const float mc = m_run[mt] * p.c;
+#pragma unroll
+            for (int u = 0; u < NSUB; ++u)
+#pragma unroll
+                for (int t = 0; t < 2; ++t) {
+                    float e[4];
+#pragma unroll
+                    for (int v = 0; v < 4; ++v) e[v] = __builtin_amdgcn_exp2f(fmaf(sc[u][t][v], p.c, -mc));
+                    l_run[mt] += (e[0] + e[1]) + (e[2] + e[3]);
+                    pb[mt][u].u[2 * t] = pack_bf16(e[0], e[1]);
+                    pb[mt][u].u[2 * t + 1] = pack_bf16(e[2], e[3]);
+                }
+        }
+#pragma unroll
+        for (int u = 0; u < NSUB; ++u)
+#pragma unroll
+            for (int c = 0; c < CW; ++c) {
+                Chunk vt;                                    // value column CW (lane % 16) + c, the lane's eight keys
+#pragma unroll
+                for (int h = 0; h < 4; ++h) {
+                    const u32 a = vr[u][2 * h][c >> 1], d = vr[u][2 * h + 1][c >> 1];
+                    vt.u[h] = (c & 1) ? pack_hi(a, d) : pack_lo(a, d);
+                }
+#pragma unroll
+                for (int mt = 0; mt < MT; ++mt)
+                    acc[mt][c] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(vt.v, pb[mt][u].v, acc[mt][c], 0, 0, 0);
+            }
+    }
+    // the wavefront's pairs to LDS: row sums over the four lane groups, outputs as [query][column]
+#pragma unroll
+    for (int mt = 0; mt < MT; ++mt) {
+        float l = l_run[mt];
+        l += __shfl_xor(l, 16);
+        l += __shfl_xor(l, 32);
+        if (g == 0) { s_ml[w][16 * mt + l16][0] = m_run[mt]; s_ml[w][16 * mt + l16][1] = l; }
+#pragma unroll
+        for (int v = 0; v < 4; ++v)
+#pragma unroll
+            for (int c = 0; c < CW; c += 4)
+                *reinterpret_cast<f32x4*>(&s_o[w][16 * mt + l16][CW * (4 * g + v) + c]) =
+                    f32x4{acc[mt][c][v], acc[mt][c + 1][v], acc[mt][c + 2][v], acc[mt][c + 3][v]};
+    }
+    __syncthreads();
+    // the four wavefronts' pairs -> the workgroup's pair (wavefront 0 always has a key: its exponent is finite)
+    for (int i = threadIdx.x; i < 16 * MT * DV / 4; i += 256) {
+        const int q = i / (DV / 4), col = 4 * (i % (DV / 4));
+        if (q >= p.M) break;
+        float mw[4], mm = -INFINITY;
+#pragma unroll
+        for (int u = 0; u < 4; ++u) { mw[u] = s_ml[u][q][0]; mm = fmaxf(mm, mw[u]); }
+        f32x4 o = {0.f, 0.f, 0.f, 0.f};
+        float l = 0.f;
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            const float ww = (mw[u] == mm) ? 1.f : __builtin_amdgcn_exp2f((mw[u] - mm) * p.c);
+            o += *reinterpret_cast<const f32x4*>(&s_o[u][q][col]) * ww;
+            l = fmaf(s_ml[u][q][1], ww, l);
+        }
+        const size_t row = (size_t)b * p.M + q;
+        if (p.nsplit == 1) {
+            const float inv = 1.0f / l;
+            const u32x2 d = {pack_bf16(o[0] * inv, o[1] * inv), pack_bf16(o[2] * inv, o[3] * inv)};
+            *reinterpret_cast<u32x2*>(p.O + row * DV + col) = d;
+        } else {
+            const size_t slot = row * p.nsplit + split;
+            cstore16f(p.part + slot * DV + col, o);
+            if (col == 0) cstore8(p.ml + 2 * slot, __float_as_uint(mm), __float_as_uint(l));
+        }
+    }
+    if (p.cnt == nullptr) return;          // one workgroup per problem, or the combine kernel follows
+    // count the delivery; the last workgroup of the problem adds the slots (a wavefront per row, in slot order)
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
+    __builtin_amdgcn_s_waitcnt(0);
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        const unsigned old = __hip_atomic_fetch_add(p.cnt + b, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        last_arrival = (old + 1u == (unsigned)p.nsplit) ? 1u : 0u;
+    }
+    __syncthreads();
+    if (last_arrival == 0u) return;
+    for (int q = w; q < p.M; q += 4)
+        attention_combine_row<DV>(p.part, p.ml, p.O, (size_t)b * p.M + q, p.nsplit, p.c, lane);
+    if (threadIdx.x == 0) __hip_atomic_store(p.cnt + b, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
 // One wavefront per query row (the launch that follows attention_kernel<..., KSPLIT>).

@@ -39,4 +39,13 @@ void attn_decode_launch(dim3 grid, hipStream_t st, const AttnArgs& a) {
     hipLaunchKernelGGL((attention_decode_kernel<DK, DV>), grid, dim3(256), 0, st, a);
 }
 
+template <int DK, int DV>
+void attn_group_launch(int mt, dim3 grid, hipStream_t st, const AttnArgs& a) {
+    if (mt == 1) hipLaunchKernelGGL((attention_group_kernel<DK, DV, 1>), grid, dim3(256), 0, st, a);
+    else hipLaunchKernelGGL((attention_group_kernel<DK, DV, 2>), grid, dim3(256), 0, st, a);
+    if (a.nsplit > 1 && a.cnt == nullptr)
+        hipLaunchKernelGGL((attention_combine_kernel<DV>), dim3((unsigned)((size_t)a.B * a.M)), dim3(64), 0, st,
+                           (const float*)a.part, (const float*)a.ml, a.O, a.nsplit, a.c);
+}
+
 }  // namespace bb

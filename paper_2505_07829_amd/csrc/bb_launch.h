@@ -34,11 +34,13 @@ void stream_t_launch(int G, int lds_bytes, hipStream_t st, const StreamTArgs& a)
 // fully fused nest for small model dimensions: ffn_nest_kernel<nd>, nd = blocks of 128 model channels (2 or 4)
 void nest_launch(int nd, int grid, hipStream_t st, const NestArgs& a);
 
-// attention: tiled kernel (ksplit > 1: split keys + combine kernel), one-query streaming kernel
+// attention: tiled kernel (ksplit > 1: split keys + combine kernel), one-query and few-query streaming kernels
 // (defined per pair of head dimensions in bb_attn_inst_*.hip)
 template <int DK, int DV>
 void attn_tiled_launch(int tail, int nw, int ksplit, dim3 grid, dim3 block, hipStream_t st, const AttnArgs& a);
 template <int DK, int DV>
 void attn_decode_launch(dim3 grid, hipStream_t st, const AttnArgs& a);
+template <int DK, int DV>       // mt = 1 or 2 groups of 16 queries
+void attn_group_launch(int mt, dim3 grid, hipStream_t st, const AttnArgs& a);
 
 }  // namespace bb

@@ -276,3 +276,17 @@ def test_one_query_replays_from_a_captured_graph():
         assert torch.equal(out_g.view(torch.uint16), out_e.view(torch.uint16)), rep
     ref = orc.attention(Q.cpu(), K.cpu(), V.cpu())
     assert rel_err(out_g.reshape(-1, 128), ref) <= TOL
+
+
+@pytest.mark.parametrize("M,N", [(2, 1), (3, 31), (15, 33), (16, 65), (17, 127), (32, 129), (31, 1023), (2, 1024),
+                                 (16, 1025), (32, 2111), (8, 5000), (33, 1024)])
+@pytest.mark.parametrize("d,dv", [(128, 128), (64, 128), (128, 64), (64, 64)])
+def test_few_queries_edges_of_groups_and_key_blocks(M, N, d, dv):
+    # one and two groups of 16 queries, ragged last groups and key blocks, one and several workgroups per
+    # problem (the pairs added by the last workgroup, or by the second kernel when there are many), and 33
+    # queries: the tiled kernel's first; twice, for the arrival counters
+    Q, K, V = bb_inputs.make_attn(3, M, N, d, dv, seed=M + N)
+    O = [bb.bb_attention(Q.cuda(), K.cuda(), V.cuda()) for _ in range(2)]
+    torch.cuda.synchronize()
+    assert torch.equal(O[0], O[1])
+    assert rel_err(O[0].reshape(-1, dv), orc.attention(Q, K, V)) <= TOL
