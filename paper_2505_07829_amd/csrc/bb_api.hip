@@ -42,7 +42,7 @@ struct Workspace {
     size_t bytes = 0;
     bool user = false;
     size_t clean = 0;                  // leading bytes known to be zero
-    size_t attn_zone = 0;              // leading bytes that hold arrival counters of bb_attention, all zero
+    size_t attn_zone = 0;              // leading bytes that hold arrival counters, all zero
     int device = -1;
 } g_ws;
 
@@ -358,8 +358,8 @@ size_t split_bytes(int mode, int64_t M, int64_t N, int64_t K, int cus) {
 // Key splits of the attention kernel for `wgs` (problem, query block) pairs and nt key blocks:
 // the largest divisor of nt that keeps about two workgroups per compute unit and at least two
 // key blocks per workgroup; 1 = no split (enough workgroups already, or a short sequence).
-// arrival counters of attention_decode_kernel, one per problem, at the workspace's start
-size_t attn_zone_bytes(int64_t B) { return align_up((size_t)B * 4); }
+// arrival counters, n words at the workspace's start
+size_t counter_bytes(int64_t n) { return align_up((size_t)n * 4); }
 
 // One query per problem: blocks of 64 keys per wavefront of attention_decode_kernel (a workgroup has four), so
 // that the launch has about three workgroups per compute unit; *nsplit = workgroups per problem.
@@ -528,6 +528,17 @@ int launch_gemm(const u16* A, int lda, const u16* B0, const u16* B1, int ldb, u1
     BB_HIP(hipGetLastError());
     prof_mark(MODE == MODE_GATEUP ? "gemm_gateup" : MODE == MODE_GATEUP_PRE ? "gemm_gateup_prescaled"
               : MODE == MODE_LN ? "gemm_ln" : MODE == MODE_LN_PRE ? "gemm_ln_prescaled" : "gemm_plain", st);
+    return BB_OK;
+}
+
+// Arrival counters must be zero when a launch begins, and every launch leaves its own at zero.  What lies behind them
+// is scratch of the launch about to be made, so afterwards no more than `zone` bytes are known to be zero.
+int prepare_counters(size_t zone, hipStream_t st) {
+    const size_t had = g_ws.attn_zone;
+    mark_dirty(0);
+    if (had < zone)
+        if (int rc = fill_zero(g_ws.ptr, zone, st)) return rc;
+    g_ws.attn_zone = zone;
     return BB_OK;
 }
 
@@ -1076,16 +1087,9 @@ int bb_attention(const void* Q, const void* K, const void* V, void* O, int64_t B
         a.part = nullptr;
         a.ml = nullptr;
         if (one || nsplit > 1) {
-            const size_t zone = attn_zone_bytes(B), pbytes = align_up((size_t)B * M * nsplit * dv * 4);
+            const size_t zone = counter_bytes(B), pbytes = align_up((size_t)B * M * nsplit * dv * 4);
             if (int rc = ensure_workspace(zone + pbytes + align_up((size_t)B * M * nsplit * 8))) return rc;
-            const size_t had = g_ws.attn_zone;
-            mark_dirty(0);
-            if (had < zone) {              // counters: zero before their first use; every launch leaves them zero
-                if (int rc = fill_zero(g_ws.ptr, zone, st)) return rc;
-                g_ws.attn_zone = zone;
-            } else {
-                g_ws.attn_zone = had;
-            }
+            if (int rc = prepare_counters(zone, st)) return rc;
             a.cnt = (unsigned*)g_ws.ptr;
             a.part = (float*)((char*)g_ws.ptr + zone);
             a.ml = (float*)((char*)g_ws.ptr + zone + pbytes);
@@ -1160,7 +1164,7 @@ size_t bb_attention_workspace_bytes(int64_t B, int64_t M, int64_t N, int64_t d, 
         if (M == 1) attn_decode_plan(B, N, kPlanCUs, &nsplit);
         else attn_group_plan(B, N, d, dv, kPlanCUs, &nsplit);
         if (M > 1 && nsplit == 1) return 0;
-        return attn_zone_bytes(B) + align_up((size_t)B * M * nsplit * dv * 4) + align_up((size_t)B * M * nsplit * 8);
+        return counter_bytes(B) + align_up((size_t)B * M * nsplit * dv * 4) + align_up((size_t)B * M * nsplit * 8);
     }
     const int s = attn_key_splits(B * ((M + 127) / 128), (N + ATTN_BK - 1) / ATTN_BK, kPlanCUs);
     if (s < 2) return 0;

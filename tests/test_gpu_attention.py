@@ -290,3 +290,18 @@ def test_few_queries_edges_of_groups_and_key_blocks(M, N, d, dv):
     torch.cuda.synchronize()
     assert torch.equal(O[0], O[1])
     assert rel_err(O[0].reshape(-1, dv), orc.attention(Q, K, V)) <= TOL
+
+
+@pytest.mark.parametrize("M", [1, 4])
+def test_arrival_counters_after_a_call_with_fewer_problems(M):
+    # many problems, few, many again: the few problems' partial results lie where the many had their counters
+    # (M = 4: 1024 keys, two workgroups per problem)
+    big, small = bb_inputs.make_attn(500, M, 1024, 64, 64, seed=1), bb_inputs.make_attn(3, M, 4096, 64, 64, seed=2)
+    big = [t.cuda() for t in big]
+    O1 = bb.bb_attention(*big)
+    Os = bb.bb_attention(*[t.cuda() for t in small])
+    O2 = torch.zeros_like(O1)
+    bb.bb_attention(*big, O=O2)
+    torch.cuda.synchronize()
+    assert torch.equal(O1, O2)
+    assert rel_err(Os.reshape(-1, 64), orc.attention(*small)) <= TOL
