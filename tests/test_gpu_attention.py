@@ -296,7 +296,7 @@ def test_few_queries_edges_of_groups_and_key_blocks(M, N, d, dv):
 def test_arrival_counters_after_a_call_with_fewer_problems(M):
     # many problems, few, many again: the few problems' partial results lie where the many had their counters
     # (M = 4: 1024 keys, two workgroups per problem)
-    big, small = bb_inputs.make_attn(500, M, 1024, 64, 64, seed=1), bb_inputs.make_attn(3, M, 4096, 64, 64, seed=2)
+    big, small = bb_inputs.make_attn(200, M, 1024, 64, 64, seed=1), bb_inputs.make_attn(3, M, 4096, 64, 64, seed=2)
     big = [t.cuda() for t in big]
     O1 = bb.bb_attention(*big)
     Os = bb.bb_attention(*[t.cuda() for t in small])
