@@ -93,8 +93,16 @@ typedef enum bb_status {
  *                       (M D bf16 written and read).  For LN -> matmul the row
  *                       kernel writes bf16(x gamma), the means and the inverse
  *                       standard deviations (two passes over the row), the
- *                       product keeps the epilogue r (P - mu c) + b.  A
- *                       candidate of the measured selection below.
+ *                       product keeps the epilogue r (P - mu c) + b.  Up to
+ *                       256 rows (LN -> matmul: 254) the products run as the
+ *                       FEW-ROW program: the row kernel, then per product one
+ *                       pass over the weights cut into equal shares for all
+ *                       compute units (fp32 partial sums, added in fixed order
+ *                       by a small kernel that applies the epilogue); gamma and
+ *                       beta are two more rows of LN's product and yield its
+ *                       column vectors.  A workspace too small for the partial
+ *                       sums keeps the tiled program.  A candidate of the
+ *                       measured selection below.
  * BB_VARIANT_NEST      (FFN with D <= 512) the LAST snapshot of Example 3, the
  *                       fully fused nest of the listing after Step 26, with one
  *                       block of output columns (N = 1: the case of the
@@ -114,11 +122,13 @@ typedef enum bb_status {
  *                       hidden blocks at once).
  * BB_VARIANT_AUTO      the measured selection for exactly this shape if
  *                       bb_*_tune has recorded one, else NEST for D <= 256,
- *                       F <= 768 and M <= 4096, else STREAM for M <= 32,
- *                       SNAPSHOT1 up to 255 rows and PRESCALE from 256 rows on
- *                       (the table measured on an MI355X for D = 4096,
- *                       F = 11008); LN -> matmul: SNAPSHOT1 up to 255 rows,
- *                       PRESCALE from 256 on.
+ *                       F <= 768 and M <= 4096, else the few-row program of
+ *                       PRESCALE up to 255 rows (any M; beyond 32 rows from
+ *                       D F = 2^19 on, below that SNAPSHOT1) and the tiled
+ *                       PRESCALE from 256 rows on; LN -> matmul: the few-row
+ *                       program up to 254 rows, PRESCALE beyond.  Where the
+ *                       workspace has no room for the few-row program: STREAM
+ *                       for M <= 32, else SNAPSHOT1 below 256 rows.
  */
 typedef enum bb_variant {
     BB_VARIANT_AUTO = 0,
@@ -175,13 +185,13 @@ int bb_rmsnorm_swiglu_ffn(const void* X, const void* g, const void* W1,
  *   X [M, D] in   gamma [D] in   beta [D] in   W [D, N] in   Y [M, N] out
  *
  * D and N positive multiples of 8, M >= 0.  With the statistics inside the
- * product loop (BB_VARIANT_SNAPSHOT1: AUTO's choice below 256 rows) the
+ * product loop (BB_VARIANT_SNAPSHOT1) the
  * variance is the one-pass form sum(x^2)/D - mean^2 in fp32: rows whose
- * |mean|/std exceeds a few hundred lose accuracy.  BB_VARIANT_PRESCALE (AUTO
- * from 256 rows on) takes two passes over the row (mean, then the sum of
- * squared deviations) and has no such limit, so the two sides of the row
- * threshold differ on such inputs; a caller with large means selects
- * BB_VARIANT_PRESCALE or BB_VARIANT_UNFUSED for every M.  Workspace: bb_workspace_bytes(
+ * |mean|/std exceeds a few hundred lose accuracy.  BB_VARIANT_PRESCALE (what
+ * AUTO runs unless the workspace is too small for its few-row program) takes
+ * two passes over the row (mean, then the sum of squared deviations) and has no
+ * such limit.  The transposed entry point with D < 512 and less than 256 rows
+ * keeps the one-pass form.  Workspace: bb_workspace_bytes(
  * BB_OP_LAYERNORM_MATMUL, M, D, N) (fp32 column vectors of length N and their
  * partial sums).
  */
@@ -201,15 +211,16 @@ int bb_layernorm_matmul(const void* X, const void* gamma, const void* beta,
  * Everything else (arguments, arithmetic, results, workspace of the op without
  * the suffix, errors) is as for bb_rmsnorm_swiglu_ffn / bb_layernorm_matmul.
  * The contraction index is contiguous in these layouts, so the weight tiles
- * need no transposition on chip.  The FFN with at most 16 rows runs a
+ * need no transposition on chip.  The FFN with at most 16 rows and D F < 24 * 2^20 runs a
  * weight-streaming kernel of its own for this layout (every workgroup owns a
  * contiguous range of rows of W1t, W3t and then of W2t: no partial sums between
  * workgroups, one grid barrier), unless bb_set_variant selected a tiled variant
  * or the shape gives a workgroup more than 128 hidden units or output columns
  * (F or D above 128 times the number of compute units); more rows, and
- * bb_layernorm_matmul_t at any size, go through the tiled kernels (for few rows
- * with the split contraction, from 256 rows on with the statistics loop as a
- * kernel of its own, see BB_VARIANT_PRESCALE).
+ * larger weights, go through the few-row program up to 255 rows (see
+ * BB_VARIANT_PRESCALE; D F >= 2^19, LN: D >= 512 and M <= 254) and else through
+ * the tiled kernels (for few rows with the split contraction, from 256 rows on
+ * with the statistics loop as a kernel of its own).
  */
 int bb_rmsnorm_swiglu_ffn_t(const void* X, const void* g, const void* W1t,
                             const void* W3t, const void* W2t, void* Y,
@@ -442,7 +453,8 @@ int bb_last_hip_error(void); /* raw hipError_t of the last BB_ERR_HIP, else 0 */
  * issued so far.
  * bb_check_fault:          BB_OK, or BB_ERR_TIMEOUT once per failure.
  * bb_debug_inject_fault:   sets the flag from the host (tests of the path above).
- * bb_debug_set_spin_limit: polls after which a wait gives up (default 8000000;
+ * bb_debug_set_spin_limit: polls after which a wait gives up (with another limit
+ *   than the default AUTO keeps to STREAM up to 32 rows; default 8000000;
  *                          0 = every wait that is not satisfied at once gives
  *                          up, for tests: every kernel still runs to its end).
  */

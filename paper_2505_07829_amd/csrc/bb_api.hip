@@ -13,6 +13,7 @@
 #include "../../include/bb.h"
 #define BB_HOST_ONLY        // the streaming kernels themselves are compiled in bb_stream_inst.hip
 #include "bb_attn.h"
+#include "bb_few.h"
 #include "bb_gemm.h"
 #include "bb_launch.h"
 #include "bb_misc.h"
@@ -30,6 +31,11 @@ constexpr int64_t kPrescaleFloorM = 16; // up to this many rows no room is plann
 constexpr int64_t kNestAutoMaxD = 256, kNestAutoMaxF = 768, kNestAutoMaxM = 16 * 256;   // shapes on which AUTO runs the fully fused nest
 constexpr int64_t kPrescaleMinM = 256; // rows from which AUTO runs the statistics loop as a kernel of its own
 constexpr int64_t kGroupOwnSlots = 128;  // partial results of one problem that its last workgroup adds itself
+constexpr int kFewMinItems = 4;        // items of a workgroup of the few-row kernel, where the contraction has as many
+constexpr int64_t kFewMinDF = 1 << 19;         // weights [D, F] from which the few-row FFN beats the tiled kernels
+constexpr int64_t kFewMinStreamTDF = 24 << 20; // and, up to 16 rows, the streaming kernel for transposed weights
+constexpr int64_t kFewMinLnTD = 512;           // model dimension from which the few-row LN beats them on transposed weights
+constexpr int kVariantFew = -2;        // AUTO's few-row program (not a variant a caller can force by number)
 constexpr size_t kAlign = 256;
 
 std::mutex g_mu;
@@ -80,7 +86,8 @@ struct DeviceInfo {
 // device the library is loaded on holds its own copy until the process ends.  In host code this name is a
 // stand-in, not an address: the device address comes from hipGetSymbolAddress (current_device_info).
 __device__ __align__(256) unsigned char scratch[BB_STATIC_SCRATCH_BYTES];
-unsigned g_spin_limit = 8000000u;      // polls after which a wait on another workgroup gives up (about two seconds)
+constexpr unsigned kSpinLimit = 8000000u;
+unsigned g_spin_limit = kSpinLimit;    // polls after which a wait on another workgroup gives up (about two seconds)
 
 bool log_on() {
     if (g_log < 0) g_log = std::getenv("BB_LOG") ? 1 : 0;
@@ -157,6 +164,8 @@ struct TuneKey {
 };
 std::map<TuneKey, int> g_tuned;
 
+bool few_applies(int op, int64_t M, int64_t D, int64_t FN);
+
 // AUTO: a measured selection for exactly this shape if there is one, else the rule of thumb
 // (the fully fused nest for small weight matrices, else the weight-streaming kernel up to kStreamMaxM rows and
 // the tiled kernels beyond; LN always fused)
@@ -173,9 +182,28 @@ int auto_variant(int op, int64_t M, int64_t D, int64_t FN) {
         // D > 256 (four pairs, twice the steps per block) nowhere: left to the measured selection.  Beyond 4096 rows
         // (more blocks of 16 rows than compute units: a second round) the tiled kernels win again.
         if (D <= kNestAutoMaxD && FN <= kNestAutoMaxF && M <= kNestAutoMaxM) return BB_VARIANT_NEST;
+        // The few-row program (five launches) : the streaming kernel (one launch with grid barriers) or, beyond 32
+        // rows, the tiled kernels, us, D x F:
+        //            256 x 1024  1024 x 2816  2880 x 7680  4096 x 11008  8192 x 16384
+        //     1 row                            36.7 : 46.8   59.8 : 60.3   135 : 142
+        //   16 rows                            39.3 : 49.5   62.4 : 62.5   140 : 142
+        //   32       21.8 : 38.6  22.4 : 50.6  42.4 : 57.0   66.7 : 72.8   141 : 153
+        //   48       22.1 : 21.1  24.1 : 30.2  45.2 : 54.7   70.3 : 86.8   145 : 180
+        //  100       22.1 : 22.2  29.9 : 36.3  54.0 : 61.2   83.4 : 93.6   176 : 193
+        //  192       24.9 : 23.2  38.2 : 40.6  72.0 : 77.2    106 : 127    227 : 273
+        //  256       28.2 : 25.4  39.4 : 39.6  87.0 : 94.6    130 : 130    277 : 272
+        // (With another poll limit than its own, set through the hook that exists to exercise the waits of the streaming
+        // kernels, AUTO keeps to the program that has such waits.)
+        const bool waits = M <= kStreamMaxM && g_spin_limit != kSpinLimit;
+        if (!waits && few_applies(op, M, D, FN) && M < kPrescaleMinM && (M <= kStreamMaxM || D * FN >= kFewMinDF))
+            return kVariantFew;
         if (M <= kStreamMaxM) return BB_VARIANT_STREAM;
         return M >= kPrescaleMinM ? BB_VARIANT_PRESCALE : BB_VARIANT_SNAPSHOT1;
     }
+    // (layer norm, few-row : tiled kernel, which needs the column vectors from a pass of its own over the weights and
+    // leaves most of the chip idle: D x N 256 x 1024 16 : 16 us, 2048 x 2048 16 : 44, 4096 x 12288 31 : 87, 8192 x 8192
+    // 35 : 155 at 16 rows; 16 : 17, 28 : 47, 58 : 102, 66 : 177 at 254)
+    if (few_applies(op, M, D, FN)) return kVariantFew;
     return M >= kPrescaleMinM ? BB_VARIANT_PRESCALE : BB_VARIANT_SNAPSHOT1;
 }
 
@@ -355,6 +383,45 @@ size_t split_bytes(int mode, int64_t M, int64_t N, int64_t K, int cus) {
 }
 
 
+// Few rows, one pass over the weights (few_rows_kernel): Mr rows (LN: gamma and beta are two of them) times `mats`
+// weight matrices [K, N].
+struct FewPlan {
+    int mt, grid, tiles;
+    size_t part_bytes;
+    FewArgs a;
+};
+FewPlan few_plan(int64_t Mr, int64_t N, int64_t K, int mats, int G) {
+    FewPlan f{};
+    f.mt = (int)((Mr + 63) / 64);
+    FewArgs& a = f.a;
+    a.Mr = (int)Mr; a.N = (int)N; a.K = (int)K;
+    a.tiles_n = (int)((N + FEW_COLS - 1) / FEW_COLS);
+    a.nk = (int)((K + GEMM_BK - 1) / GEMM_BK);
+    f.tiles = mats * a.tiles_n;
+    a.items = f.tiles * a.nk;
+    a.per = std::max((a.items + G - 1) / G, std::min(a.nk, kFewMinItems));
+    a.slots = (a.nk - 1) / a.per + 2;
+    f.grid = (a.items + a.per - 1) / a.per;
+    f.part_bytes = align_up((size_t)f.tiles * a.slots * Mr * FEW_COLS * 4);
+    return f;
+}
+bool few_applies(int op, int64_t M, int64_t D, int64_t FN) {
+    // (32-bit byte offsets into the weights and the rows)
+    if ((size_t)D * FN * 2 >= (1ull << 32) || (size_t)(M + 2) * std::max(D, FN) * 2 >= (1ull << 32)) return false;
+    if (op == BB_OP_LAYERNORM_MATMUL) return M + 2 <= 64 * FEW_MAXMT;
+    return op == BB_OP_RMSNORM_SWIGLU_FFN && M <= 64 * FEW_MAXMT;
+}
+// scratch of the few-row programs.  FFN: hidden | partial sums (of one product at a time) | gain-scaled X | inverse norms;
+// LN: partial sums | gamma-scaled X, gamma, beta | row statistics
+size_t few_bytes(int op, int64_t M, int64_t D, int64_t FN) {
+    if (!few_applies(op, M, D, FN)) return 0;
+    if (op == BB_OP_LAYERNORM_MATMUL)
+        return few_plan(M + 2, FN, D, 1, kPlanCUs).part_bytes + align_up((size_t)(M + 2) * D * 2) + align_up((size_t)M * 8);
+    return align_up((size_t)M * FN * 2) +
+           std::max(few_plan(M, FN, D, 2, kPlanCUs).part_bytes, few_plan(M, D, FN, 1, kPlanCUs).part_bytes) +
+           align_up((size_t)M * D * 2) + align_up((size_t)M * 4);
+}
+
 // Key splits of the attention kernel for `wgs` (problem, query block) pairs and nt key blocks:
 // the largest divisor of nt that keeps about two workgroups per compute unit and at least two
 // key blocks per workgroup; 1 = no split (enough workgroups already, or a short sequence).
@@ -435,6 +502,12 @@ int ensure_workspace(size_t need) {
     g_ws.device = dev;
     if (log_on()) std::fprintf(stderr, "[bb] workspace %zu bytes allocated\n", need);
     return BB_OK;
+}
+
+// The few-row program of `op` runs: its scratch behind `zone` fits the workspace.  A caller's buffer that was sized for
+// the tiled programs only keeps them.
+bool few_fits(int op, int64_t M, int64_t D, int64_t FN, size_t zone) {
+    return few_applies(op, M, D, FN) && !(g_ws.user && g_ws.bytes < zone + few_bytes(op, M, D, FN));
 }
 
 int fill_zero(void* p, size_t bytes, hipStream_t st) {
@@ -529,6 +602,52 @@ int launch_gemm(const u16* A, int lda, const u16* B0, const u16* B1, int ldb, u1
     prof_mark(MODE == MODE_GATEUP ? "gemm_gateup" : MODE == MODE_GATEUP_PRE ? "gemm_gateup_prescaled"
               : MODE == MODE_LN ? "gemm_ln" : MODE == MODE_LN_PRE ? "gemm_ln_prescaled" : "gemm_plain", st);
     return BB_OK;
+}
+
+// C = epilogue(A B) for few rows: the weight stream, then the sum of its shares.  Returns through hipGetLastError.
+int launch_few(int mode, bool bt, const u16* A, const u16* B0, const u16* B1, int Mr, int N, int K, float* part,
+               const float* rowstat, u16* C, int M, const u16* res, hipStream_t st) {
+    FewPlan f = few_plan(Mr, N, K, B1 ? 2 : 1, kPlanCUs);
+    f.a.A = A; f.a.B0 = B0; f.a.B1 = B1; f.a.part = part;
+    if (log_on())
+        std::fprintf(stderr, "[bb] few rows mode %d%s rows %d N %d K %d: %d x %d of %d items\n", mode,
+                     bt ? " (B transposed)" : "", Mr, N, K, f.grid, f.a.per, f.a.items);
+    few_rows_launch(f.mt, bt, f.grid, st, f.a);
+    BB_HIP(hipGetLastError());
+    few_reduce_launch(mode, st, f.a, rowstat, C, M, res);
+    BB_HIP(hipGetLastError());
+    prof_mark(mode == MODE_GATEUP_PRE ? "few_gateup" : mode == MODE_LN_PRE ? "few_ln" : "few_plain", st);
+    return BB_OK;
+}
+
+int ffn_few(bool bt, const u16* X, const u16* g, const u16* W1, const u16* W3, const u16* W2, const u16* R, u16* Y,
+            int64_t M, int64_t D, int64_t F, float eps, size_t zone, hipStream_t st) {
+    u16* H = (u16*)((char*)g_ws.ptr + zone);
+    float* part = (float*)((char*)H + align_up((size_t)M * F * 2));
+    u16* Xg = (u16*)((char*)part + std::max(few_plan(M, F, D, 2, kPlanCUs).part_bytes, few_plan(M, D, F, 1, kPlanCUs).part_bytes));
+    float* rstd = (float*)((char*)Xg + align_up((size_t)M * D * 2));
+    mark_dirty(zone);
+    prof_begin(st);
+    hipLaunchKernelGGL(rms_gain_rows_kernel, dim3((unsigned)M), dim3(256), 0, st, X, g, Xg, rstd, (int)D, eps);
+    BB_HIP(hipGetLastError());
+    prof_mark("rms_gain_rows", st);
+    if (int rc = launch_few(MODE_GATEUP_PRE, bt, Xg, W1, W3, (int)M, (int)F, (int)D, part, rstd, H, (int)M, nullptr, st))
+        return rc;
+    return launch_few(MODE_PLAIN, bt, H, W2, nullptr, (int)M, (int)D, (int)F, part, nullptr, Y, (int)M, R, st);
+}
+
+int ln_few(bool bt, const u16* X, const u16* gamma, const u16* beta, const u16* W, u16* Y, int64_t M, int64_t D,
+           int64_t N, float eps, hipStream_t st) {
+    float* part = (float*)g_ws.ptr;
+    u16* Xg = (u16*)((char*)part + few_plan(M + 2, N, D, 1, kPlanCUs).part_bytes);
+    float* stat = (float*)((char*)Xg + align_up((size_t)(M + 2) * D * 2));
+    mark_dirty(0);
+    prof_begin(st);
+    hipLaunchKernelGGL(ln_gain_rows_kernel, dim3((unsigned)(M + 2)), dim3(256), 0, st, X, gamma, beta, Xg, stat, (int)M,
+                       (int)D, eps);
+    BB_HIP(hipGetLastError());
+    prof_mark("ln_gain_rows", st);
+    return launch_few(MODE_LN_PRE, bt, Xg, W, nullptr, (int)M + 2, (int)N, (int)D, part, stat, Y, (int)M, nullptr, st);
 }
 
 // Arrival counters must be zero when a launch begins, and every launch leaves its own at zero.  What lies behind them
@@ -788,7 +907,7 @@ int bb_debug_set_spin_limit(unsigned polls) {
 size_t bb_workspace_bytes(int op, int64_t M, int64_t D, int64_t F) {
     if (op < BB_OP_RMSNORM_SWIGLU_FFN || op > BB_OP_LAYERNORM_MATMUL_UNFUSED) return 0;
     if (check_dims(M, D, F) != BB_OK) return 0;
-    return zone_bytes(op, M, D, F) + scratch_bytes(op, M, D, F);
+    return zone_bytes(op, M, D, F) + std::max(scratch_bytes(op, M, D, F), few_bytes(op, M, D, F));
 }
 
 int bb_set_workspace(void* dptr, size_t bytes) {
@@ -860,8 +979,17 @@ int ffn_locked(int variant, const void* X, const void* g, const void* W1, const 
         return BB_OK;
     }
     const size_t zone = zone_bytes(BB_OP_RMSNORM_SWIGLU_FFN, M, D, F);
-    if (int rc = ensure_workspace(zone + scratch_bytes(BB_OP_RMSNORM_SWIGLU_FFN, M, D, F))) return rc;
+    const bool few = (variant == kVariantFew || variant == BB_VARIANT_PRESCALE) &&
+                     few_fits(BB_OP_RMSNORM_SWIGLU_FFN, M, D, F, zone);
+    if (variant == kVariantFew && !few)        // a caller's buffer has no room for it
+        variant = M <= kStreamMaxM ? BB_VARIANT_STREAM : M >= kPrescaleMinM ? BB_VARIANT_PRESCALE : BB_VARIANT_SNAPSHOT1;
+    const size_t scratch = scratch_bytes(BB_OP_RMSNORM_SWIGLU_FFN, M, D, F);
+    if (int rc = ensure_workspace(zone + (few ? std::max(scratch, few_bytes(BB_OP_RMSNORM_SWIGLU_FFN, M, D, F)) : scratch)))
+        return rc;
     hipStream_t st = as_stream(stream);
+    if (few)
+        return ffn_few(false, (const u16*)X, (const u16*)g, (const u16*)W1, (const u16*)W3, (const u16*)W2,
+                       (const u16*)R, (u16*)Y, M, D, F, eps, zone, st);
     const u16 *x = (const u16*)X, *gg = (const u16*)g, *w1 = (const u16*)W1, *w3 = (const u16*)W3,
               *w2 = (const u16*)W2;
     if (variant == BB_VARIANT_STREAM)
@@ -900,15 +1028,26 @@ int ffn_t_locked(const void* X, const void* g, const void* W1t, const void* W3t,
     if (int rc = current_device_info(&dev)) return rc;
     if (int rc = check_fault(dev)) return rc;
     const size_t zone = zone_bytes(BB_OP_RMSNORM_SWIGLU_FFN, M, D, F);
-    if (int rc = ensure_workspace(zone + scratch_bytes(BB_OP_RMSNORM_SWIGLU_FFN, M, D, F))) return rc;
+    const int variant = read_variant();
+    // The few-row program : the streaming kernel up to 16 rows, us: 2048 x 5632 (D x F) 29.3 : 26.1, 2880 x 7680 38.6 :
+    // 38.4, 4096 x 11008 58.8 : 58.9 (1 row 55.7 : 57.4), 4096 x 14336 76 : 86, 8192 x 16384 134 : 155; beyond 16 rows
+    // : the tiled kernels: 256 x 1024 22 : 21, 512 x 1408 22 : 25, 4096 x 11008 59 : 89, 8192 x 16384 137 : 227.
+    const bool few = (variant == BB_VARIANT_AUTO || variant == BB_VARIANT_PRESCALE) && M < kPrescaleMinM &&
+                     D * F >= (M <= kStreamTMaxM ? kFewMinStreamTDF : kFewMinDF) &&
+                     few_fits(BB_OP_RMSNORM_SWIGLU_FFN, M, D, F, zone);
+    const size_t scratch = scratch_bytes(BB_OP_RMSNORM_SWIGLU_FFN, M, D, F);
+    if (int rc = ensure_workspace(zone + (few ? std::max(scratch, few_bytes(BB_OP_RMSNORM_SWIGLU_FFN, M, D, F)) : scratch)))
+        return rc;
     hipStream_t st = as_stream(stream);
     // few rows: the weight-streaming kernel for this layout (unless a tiled variant is forced)
-    const int variant = read_variant();
-    if (M <= kStreamTMaxM && (variant == BB_VARIANT_AUTO || variant == BB_VARIANT_STREAM)) {
+    if (!few && M <= kStreamTMaxM && (variant == BB_VARIANT_AUTO || variant == BB_VARIANT_STREAM)) {
         const int rc = run_stream_t((const u16*)X, (const u16*)g, (const u16*)W1t, (const u16*)W3t, (const u16*)W2t,
                                     (const u16*)R, (u16*)Y, (int)M, (int)D, (int)F, eps, dev, st);
         if (rc != BB_ERR_VARIANT) return rc;
     }
+    if (few)
+        return ffn_few(true, (const u16*)X, (const u16*)g, (const u16*)W1t, (const u16*)W3t, (const u16*)W2t,
+                       (const u16*)R, (u16*)Y, M, D, F, eps, zone, st);
     u16* H = (u16*)((char*)g_ws.ptr + zone);
     void* split = (char*)H + align_up((size_t)M * F * 2);
     const int pcus = std::min(dev->cus, kPlanCUs);
@@ -941,8 +1080,14 @@ int ln_locked(int variant, const void* X, const void* gamma, const void* beta, c
     if (variant == BB_VARIANT_UNFUSED) return ln_unfused_locked(X, gamma, beta, W, Y, M, D, N, eps, stream);
     const DeviceInfo* dev = nullptr;
     if (int rc = current_device_info(&dev)) return rc;
-    if (int rc = ensure_workspace(scratch_bytes(BB_OP_LAYERNORM_MATMUL, M, D, N))) return rc;
+    const bool few = (variant == kVariantFew || variant == BB_VARIANT_PRESCALE) &&
+                     few_fits(BB_OP_LAYERNORM_MATMUL, M, D, N, 0);
+    if (variant == kVariantFew && !few) variant = BB_VARIANT_SNAPSHOT1;        // a caller's buffer has no room for it
+    const size_t scratch = scratch_bytes(BB_OP_LAYERNORM_MATMUL, M, D, N);
+    if (int rc = ensure_workspace(few ? std::max(scratch, few_bytes(BB_OP_LAYERNORM_MATMUL, M, D, N)) : scratch)) return rc;
     hipStream_t st = as_stream(stream);
+    if (few)
+        return ln_few(false, (const u16*)X, (const u16*)gamma, (const u16*)beta, (const u16*)W, (u16*)Y, M, D, N, eps, st);
     mark_dirty(0);
     float* colc = (float*)g_ws.ptr;
     float* colb = (float*)((char*)g_ws.ptr + align_up((size_t)N * 4));
@@ -961,7 +1106,7 @@ int ln_locked(int variant, const void* X, const void* gamma, const void* beta, c
         u16* Xg = (u16*)((char*)g_ws.ptr + (2 + 2 * COLVEC_SPLITS) * align_up((size_t)N * 4));
         float* stat = (float*)((char*)Xg + align_up((size_t)M * D * 2));
         hipLaunchKernelGGL(ln_gain_rows_kernel, dim3((unsigned)M), dim3(256), 0, st, (const u16*)X,
-                           (const u16*)gamma, Xg, stat, (int)D, eps);
+                           (const u16*)gamma, (const u16*)beta, Xg, stat, (int)M, (int)D, eps);
         BB_HIP(hipGetLastError());
         prof_mark("ln_gain_rows", st);
         return launch_gemm<MODE_LN_PRE>(Xg, (int)D, (const u16*)W, nullptr, (int)N, (u16*)Y, (int)N, nullptr, colc,
@@ -1022,8 +1167,13 @@ int bb_layernorm_matmul_t(const void* X, const void* gamma, const void* beta, co
     std::lock_guard<std::mutex> lk(g_mu);
     const DeviceInfo* dev = nullptr;
     if (int rc = current_device_info(&dev)) return rc;
-    if (int rc = ensure_workspace(scratch_bytes(BB_OP_LAYERNORM_MATMUL, M, D, N))) return rc;
+    // (few-row : tiled, us: 256 x 1024 16 : 13.5 (D x N; one launch more), 2048 x 2048 16 : 36, 4096 x 12288 28 : 82)
+    const bool few = D >= kFewMinLnTD && few_fits(BB_OP_LAYERNORM_MATMUL, M, D, N, 0);
+    const size_t scratch = scratch_bytes(BB_OP_LAYERNORM_MATMUL, M, D, N);
+    if (int rc = ensure_workspace(few ? std::max(scratch, few_bytes(BB_OP_LAYERNORM_MATMUL, M, D, N)) : scratch)) return rc;
     hipStream_t st = as_stream(stream);
+    if (few)
+        return ln_few(true, (const u16*)X, (const u16*)gamma, (const u16*)beta, (const u16*)Wt, (u16*)Y, M, D, N, eps, st);
     mark_dirty(0);
     float* colc = (float*)g_ws.ptr;
     float* colb = (float*)((char*)g_ws.ptr + align_up((size_t)N * 4));
@@ -1036,7 +1186,7 @@ int bb_layernorm_matmul_t(const void* X, const void* gamma, const void* beta, co
         u16* Xg = (u16*)((char*)g_ws.ptr + (2 + 2 * COLVEC_SPLITS) * align_up((size_t)N * 4));
         float* stat = (float*)((char*)Xg + align_up((size_t)M * D * 2));
         hipLaunchKernelGGL(ln_gain_rows_kernel, dim3((unsigned)M), dim3(256), 0, st, (const u16*)X,
-                           (const u16*)gamma, Xg, stat, (int)D, eps);
+                           (const u16*)gamma, (const u16*)beta, Xg, stat, (int)M, (int)D, eps);
         BB_HIP(hipGetLastError());
         prof_mark("ln_gain_rows", st);
         return launch_gemm<MODE_LN_PRE, true>(Xg, (int)D, (const u16*)Wt, nullptr, (int)D, (u16*)Y, (int)N, nullptr,

@@ -13,6 +13,7 @@ struct StreamArgs;
 struct StreamTArgs;
 struct AttnArgs;
 struct NestArgs;
+struct FewArgs;
 
 // gemm_kernel<MODE, bm, full, odd, split, bt> on `grid` workgroups (defined per MODE and per weight
 // layout in bb_gemm_inst_*.hip); split launches exist for MODE_PLAIN and MODE_GATEUP only
@@ -23,6 +24,12 @@ void gemm_dispatch(int bm, bool full, bool odd, bool split, dim3 grid, hipStream
 void splitk_reduce_dispatch(int mode, const float* part, const float* ssqpart, unsigned short* C, int M, int N, int K,
                             int ldp, int ldc, int nsplit, float eps, const unsigned short* res, int ldr,
                             hipStream_t st);
+
+// products of up to 64 mt rows cut into equal shares of the weight stream (bt: weights transposed), and the kernel that
+// adds the shares and applies the epilogue (mode = MODE_PLAIN, MODE_GATEUP_PRE or MODE_LN_PRE)
+void few_rows_launch(int mt, bool bt, int grid, hipStream_t st, const FewArgs& a);
+void few_reduce_launch(int mode, hipStream_t st, const FewArgs& a, const float* rowstat, unsigned short* C, int M,
+                       const unsigned short* res);
 
 // streaming kernels: workgroups of the kernel one compute unit can hold (hipError_t in *err), launch
 // (row-major weights: ffn_stream_kernel<mt>, mt = 1 or 2 groups of 16 rows)

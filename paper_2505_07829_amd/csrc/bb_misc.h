@@ -98,11 +98,17 @@ __global__ __launch_bounds__(256) void layernorm_rows_kernel(const u16* X, const
 
 // The statistics loop of Example 2's first snapshot as a kernel of its own, with gamma:
 // Xg[i,:] = bf16( gamma * x ), stat[i] = (rsqrt(var + eps), mean), biased variance, two passes;
-// one workgroup per row.
-__global__ __launch_bounds__(256) void ln_gain_rows_kernel(const u16* X, const u16* gamma, u16* Xg, float* stat,
-                                                           int D, float eps) {
+// one workgroup per row.  A launch with M + 2 workgroups also copies gamma and beta to the rows M and M + 1: as rows
+// of the product's operand they yield the column vectors gamma^T W and beta^T W.
+__global__ __launch_bounds__(256) void ln_gain_rows_kernel(const u16* X, const u16* gamma, const u16* beta, u16* Xg,
+                                                           float* stat, int M, int D, float eps) {
     __shared__ float red[4];
     const size_t row = blockIdx.x;
+    if (row >= (size_t)M) {
+        const u16* const src = row == (size_t)M ? gamma : beta;
+        for (int c = threadIdx.x * 8; c < D; c += 256 * 8) *reinterpret_cast<u32x4*>(Xg + row * D + c) = ldg16(src + c);
+        return;
+    }
     const u16* x = X + row * D;
     float s = 0.f;
     for (int c = threadIdx.x * 8; c < D; c += 256 * 8) {

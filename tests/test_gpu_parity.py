@@ -719,3 +719,67 @@ def test_stream_kernels_replay_from_a_captured_graph(transposed):
         assert torch.equal(out_g.view(torch.uint16), out_e.view(torch.uint16)), rep
     ref = orc.rmsnorm_swiglu_ffn(d[0].cpu(), g, W1, W3, W2, 1e-6)
     assert row_rel_err(out_g, ref) <= TOL
+
+
+# --------------------------------------------------- few-row program (AUTO up to 255 rows; LN: 254)
+FEW_ROWS = [1, 16, 33, 64, 65, 128, 129, 192, 193, 255]      # edges of the groups of 64 rows
+
+
+@pytest.mark.parametrize("M", FEW_ROWS)
+@pytest.mark.parametrize("transposed", [False, True])
+def test_few_rows_ffn(M, transposed):
+    # ragged in the contraction of either product (520 = 8 x 64 + 8, 1032 = 16 x 64 + 8) and in the columns; up to 16
+    # rows the transposed layout takes this program for large weights only
+    D, F = (4104, 6136) if transposed and M <= 16 else (520, 1032)
+    cpu = bb_inputs.make_ffn(M, D, F, seed=M)
+    ref = orc.rmsnorm_swiglu_ffn(*cpu, 1e-6)
+    X, g, W1, W3, W2 = dev(cpu)
+    if transposed:
+        W1, W3, W2 = (w.t().contiguous() for w in (W1, W3, W2))
+    bb.bb_profile_enable(True)
+    try:
+        Y = (bb.bb_rmsnorm_swiglu_ffn_t if transposed else bb.bb_rmsnorm_swiglu_ffn)(X, g, W1, W3, W2, 1e-6)
+        names = [n for n, _ in bb.bb_profile_last()]
+    finally:
+        bb.bb_profile_enable(False)
+    assert names == ["rms_gain_rows", "few_gateup", "few_plain"], names
+    assert row_rel_err(Y, ref) <= TOL
+    # the residual joins before the one rounding
+    Yr = bb.bb_rmsnorm_swiglu_ffn_residual(X, g, W1, W3, W2, X, 1e-6, transposed=transposed)
+    assert row_rel_err(Yr, ref + cpu[0].double().numpy()) <= TOL
+
+
+@pytest.mark.parametrize("M", [1, 62, 63, 126, 127, 254])
+@pytest.mark.parametrize("D,N", [(520, 264), (1024, 2056)])
+@pytest.mark.parametrize("transposed", [False, True])
+def test_few_rows_ln(M, D, N, transposed):
+    cpu = bb_inputs.make_ln(M, D, N, seed=M)
+    ref = orc.layernorm_matmul(*cpu, 1e-5)
+    X, gamma, beta, W = dev(cpu)
+    bb.bb_profile_enable(True)
+    try:
+        Y = (bb.bb_layernorm_matmul_t(X, gamma, beta, W.t().contiguous(), 1e-5) if transposed
+             else bb.bb_layernorm_matmul(X, gamma, beta, W, 1e-5))
+        names = [n for n, _ in bb.bb_profile_last()]
+    finally:
+        bb.bb_profile_enable(False)
+    assert names == ["ln_gain_rows", "few_ln"], names
+    assert row_rel_err(Y, ref) <= TOL
+
+
+def test_few_rows_need_room():
+    # a caller's workspace that the tiled programs fit, but not this one's partial sums: what ran before runs
+    M, D, F = 250, 1024, 2048
+    cpu = bb_inputs.make_ffn(M, D, F, seed=1)
+    need = bb.bb_workspace_bytes(bb.OP_FFN, M, D, F)
+    ws = torch.zeros(need - 256, dtype=torch.uint8, device="cuda")
+    bb.bb_set_workspace(ws)
+    try:
+        err = ffn_case(cpu, 1e-6)
+        bb.bb_profile_enable(True)
+        bb.bb_rmsnorm_swiglu_ffn(*dev(cpu), 1e-6)
+        names = [n for n, _ in bb.bb_profile_last()]
+    finally:
+        bb.bb_profile_enable(False)
+        bb.bb_set_workspace(None)
+    assert names[0] == "gemm_gateup" and err <= TOL
