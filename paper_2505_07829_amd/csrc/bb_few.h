@@ -26,6 +26,7 @@ namespace bb {
 constexpr int FEW_MAXMT = 4;             // groups of 64 rows
 constexpr int FEW_THREADS = 512;         // eight wavefronts, 2 (rows) x 4 (columns)
 constexpr int FEW_COLS = 128;            // columns per tile
+constexpr int FEW_RROWS = 8;             // rows per workgroup of the reduction
 
 struct FewArgs {
     const u16* A;        // [Mr, K]
@@ -79,14 +80,17 @@ __global__ __launch_bounds__(FEW_THREADS) void few_rows_kernel(const FewArgs p) 
     const size_t bbytes = (size_t)p.K * p.N * 2;
     const int ldb = BT ? p.K : p.N;
 
-    // ---- load role (same LDS layouts as the tiled kernels).  A: instruction j fills tile rows 8 (MT w + j) + 0..7.
-    // Rows past the last one read the last row; chunks past the contraction read its last chunk (and are zeroed as
-    // fragments).
+    // ---- load role (same LDS layouts as the tiled kernels).  A: instruction j fills tile rows 8 (w + 8 j) + 0..7.
+    // Groups of eight rows past the last row are not loaded: whatever lies there only enters rows of the result that
+    // are not stored (the last group of 64 rows is the only one that can have such rows, so a wavefront issues MT or
+    // MT - 1 of these instructions).  Rows past the last one in a loaded group read the last row; chunks past the
+    // contraction read its last chunk (and are zeroed as fragments).
+    const bool allA = 8 * (w + 8 * (MT - 1)) < p.Mr;
     u32 voA[MT];
     int kcA[MT];
 #pragma unroll
     for (int j = 0; j < MT; ++j) {
-        const int row = 8 * (MT * w + j) + (lane >> 3);
+        const int row = 8 * (w + 8 * j) + (lane >> 3);
         kcA[j] = 8 * ((lane & 7) ^ ((row >> 1) & 7));
         voA[j] = (u32)min(row, p.Mr - 1) * (u32)p.K * 2u;
     }
@@ -134,7 +138,8 @@ __global__ __launch_bounds__(FEW_THREADS) void few_rows_kernel(const FewArgs p) 
                              sb + (2 * w + q) * 1024u);
             }
 #pragma unroll
-            for (int j = 0; j < MT; ++j) few_dma(rsA, voA[j] + 2u * kcA[j], (u32)k0 * 2u, sa + (MT * w + j) * 1024u);
+            for (int j = 0; j < MT; ++j)
+                if (j < MT - 1 || allA) few_dma(rsA, voA[j] + 2u * kcA[j], (u32)k0 * 2u, sa + (w + 8 * j) * 1024u);
         } else {
 #pragma unroll
             for (int q = 0; q < 2; ++q) {
@@ -144,7 +149,8 @@ __global__ __launch_bounds__(FEW_THREADS) void few_rows_kernel(const FewArgs p) 
             }
 #pragma unroll
             for (int j = 0; j < MT; ++j)
-                few_dma(rsA, voA[j] + 2u * (u32)min(k0 + kcA[j], p.K - 8), 0u, sa + (MT * w + j) * 1024u);
+                if (j < MT - 1 || allA)
+                    few_dma(rsA, voA[j] + 2u * (u32)min(k0 + kcA[j], p.K - 8), 0u, sa + (w + 8 * j) * 1024u);
         }
         ls = ls + 1 == NS ? 0 : ls + 1;
         if (++lk == p.nk) {
@@ -221,23 +227,26 @@ __global__ __launch_bounds__(FEW_THREADS) void few_rows_kernel(const FewArgs p) 
             }
     };
 
+    const bool rows_w = 32 * MT * wm < p.Mr;                     // (up to 32 rows: four wavefronts only load)
     int ct = lt, ck = lk, cs = 0;                                // the item and stage multiplied next
     for (int s = 0; s < min(n, NS - 1); ++s) issue();
     clear();
     for (int i = 0; i < n; ++i) {
         // item i has landed (all but the NS - 2 stages requested after it), and every wavefront is done with the
         // stage that the next request overwrites
-        if (i + NS - 2 < n)
+        if (i + NS - 2 < n && allA)
             asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" :: "n"((NS - 2) * NLD) : "memory");
+        else if (i + NS - 2 < n)
+            asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" :: "n"((NS - 2) * (NLD - 1)) : "memory");
         else
             asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
         __builtin_amdgcn_s_barrier();
         asm volatile("" ::: "memory");
         if (i + NS - 1 < n) issue();
-        compute(cs, item_k(ct, ck));
+        if (rows_w) compute(cs, item_k(ct, ck));
         cs = cs + 1 == NS ? 0 : cs + 1;
         if (++ck == p.nk || i == n - 1) {
-            store(ct);
+            if (rows_w) store(ct);
             clear();
             ck = 0;
             ++ct;
@@ -251,51 +260,52 @@ __global__ __launch_bounds__(FEW_THREADS) void few_rows_kernel(const FewArgs p) 
 //   MODE_LN_PRE      C = bf16(r (P - mu c) + b), (r, mu) = rowstat[2 m ...]; c and b are the rows M and M + 1 of the
 //                    product, whose operand rows are gamma and beta themselves (Rule 5's column vectors out of the
 //                    same pass over the weights)
-// One thread per ROWS rows and four consecutive columns.
+// One workgroup per tile of 128 columns and FEW_RROWS rows, a thread per row and four columns: where a tile's shares lie
+// is the same for the whole workgroup (scalar arithmetic), and the loads of all shares are in flight together - the
+// kernel is bound by its launch and one round trip to memory (4 to 5 us).
 template <int MODE>
-__global__ __launch_bounds__(256) void few_reduce_kernel(const FewArgs p, const float* rowstat, u16* C, int M,
-                                                         const u16* res) {
-    constexpr int ROWS = MODE == MODE_LN_PRE ? 2 : 1;            // (c and b are read once for both rows)
-    const u32 groups = p.N / 4, idx = blockIdx.x * 256 + threadIdx.x;
-    const int m0 = ROWS * (int)(idx / groups), c0 = 4 * (int)(idx % groups);
-    if (m0 >= M) return;
-    auto sum = [&](int tile, int m) {
-        const int first = tile * p.nk;
-        const int ns = (first + p.nk - 1) / p.per - first / p.per + 1;
-        const size_t stride = (size_t)p.Mr * FEW_COLS;
-        const float* src = p.part + ((size_t)tile * p.slots * p.Mr + m) * FEW_COLS + (c0 & (FEW_COLS - 1));
-        f32x4 s = *reinterpret_cast<const f32x4*>(src);
-#pragma unroll 4
-        for (int i = 1; i < ns; ++i) s += *reinterpret_cast<const f32x4*>(src + i * stride);
+__global__ __launch_bounds__(32 * FEW_RROWS) void few_reduce_kernel(const FewArgs p, const float* rowstat, u16* C, int M,
+                                                                   const u16* res) {
+    constexpr int BATCH = MODE == MODE_PLAIN ? 8 : 4;            // shares loaded together
+    const int tile = blockIdx.x, q4 = 4 * (threadIdx.x & 31), c0 = tile * FEW_COLS + q4;
+    const int m = min((int)(blockIdx.y * FEW_RROWS + (threadIdx.x >> 5)), M - 1);   // (the last row's threads may repeat)
+    if (c0 >= p.N) return;
+    const size_t stride = (size_t)p.Mr * FEW_COLS;
+    auto shares = [&](int tl) {
+        const u32 first = (u32)tl * p.nk, per = p.per;
+        return (int)((first + p.nk - 1) / per - first / per) + 1;
+    };
+    auto sum = [&](int tl, int ns, int row) {                    // in order, BATCH loads at a time
+        const float* const src = p.part + ((size_t)tl * p.slots * p.Mr + row) * FEW_COLS + q4;
+        f32x4 s = {0, 0, 0, 0};
+        for (int i = 0; i < ns; i += BATCH) {
+            f32x4 v[BATCH];
+#pragma unroll
+            for (int j = 0; j < BATCH; ++j) v[j] = *reinterpret_cast<const f32x4*>(src + min(i + j, ns - 1) * stride);
+#pragma unroll
+            for (int j = 0; j < BATCH; ++j)
+                if (i + j < ns) s += v[j];
+        }
         return s;
     };
-    const int tile = c0 / FEW_COLS;
-    f32x4 cc, bb_;
-    if (MODE == MODE_LN_PRE) {
-        cc = sum(tile, M);
-        bb_ = sum(tile, M + 1);
+    const int ns = shares(tile);
+    f32x4 y = sum(tile, ns, m);
+    if (MODE == MODE_GATEUP_PRE) {
+        const f32x4 q = sum(tile + p.tiles_n, shares(tile + p.tiles_n), m);
+        const float r = rowstat[m];
+#pragma unroll
+        for (int j = 0; j < 4; ++j) y[j] = swiglu(r * y[j], r * q[j]);
+    } else if (MODE == MODE_LN_PRE) {
+        const f32x4 cc = sum(tile, ns, M), cb = sum(tile, ns, M + 1);
+        const float r = rowstat[2 * m], mu = rowstat[2 * m + 1];
+#pragma unroll
+        for (int j = 0; j < 4; ++j) y[j] = fmaf(r, y[j] - mu * cc[j], cb[j]);
+    } else if (res != nullptr) {
+        const u32x2 rr = *reinterpret_cast<const u32x2*>(res + (size_t)m * p.N + c0);
+        y += f32x4{bf_lo(rr[0]), bf_hi(rr[0]), bf_lo(rr[1]), bf_hi(rr[1])};
     }
-#pragma unroll
-    for (int i = 0; i < ROWS; ++i) {
-        const int m = m0 + i;
-        if (m >= M) return;
-        f32x4 y = sum(tile, m);
-        u16* const out = C + (size_t)m * p.N + c0;
-        if (MODE == MODE_GATEUP_PRE) {
-            const f32x4 q = sum(tile + p.tiles_n, m);
-            const float r = rowstat[m];
-#pragma unroll
-            for (int j = 0; j < 4; ++j) y[j] = swiglu(r * y[j], r * q[j]);
-        } else if (MODE == MODE_LN_PRE) {
-            const float r = rowstat[2 * m], mu = rowstat[2 * m + 1];
-#pragma unroll
-            for (int j = 0; j < 4; ++j) y[j] = fmaf(r, y[j] - mu * cc[j], bb_[j]);
-        } else if (res != nullptr) {
-            const u32x2 rr = *reinterpret_cast<const u32x2*>(res + (size_t)m * p.N + c0);
-            y += f32x4{bf_lo(rr[0]), bf_hi(rr[0]), bf_lo(rr[1]), bf_hi(rr[1])};
-        }
-        *reinterpret_cast<u32x2*>(out) = u32x2{pack_bf16(y[0], y[1]), pack_bf16(y[2], y[3])};
-    }
+    if (blockIdx.y * FEW_RROWS + (threadIdx.x >> 5) < (u32)M)    // (a repeated row is not stored twice: C may be the residual)
+        *reinterpret_cast<u32x2*>(C + (size_t)m * p.N + c0) = u32x2{pack_bf16(y[0], y[1]), pack_bf16(y[2], y[3])};
 }
 #endif  // BB_HOST_ONLY
 

@@ -16,8 +16,7 @@ void few_rows_launch(int mt, bool bt, int grid, hipStream_t st, const FewArgs& a
 
 void few_reduce_launch(int mode, hipStream_t st, const FewArgs& a, const float* rowstat, u16* C, int M,
                        const u16* res) {
-    const size_t rows = mode == MODE_LN_PRE ? (M + 1) / 2 : M;
-    const dim3 grid((unsigned)((rows * (a.N / 4) + 255) / 256)), block(256);
+    const dim3 grid(a.tiles_n, (M + FEW_RROWS - 1) / FEW_RROWS), block(32 * FEW_RROWS);
     if (mode == MODE_GATEUP_PRE)
         hipLaunchKernelGGL(few_reduce_kernel<MODE_GATEUP_PRE>, grid, block, 0, st, a, rowstat, C, M, res);
     else if (mode == MODE_LN_PRE)

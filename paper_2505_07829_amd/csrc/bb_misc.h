@@ -39,6 +39,20 @@ __global__ __launch_bounds__(256) void rmsnorm_rows_kernel(const u16* X, const u
     }
 }
 
+// ROW_CHUNKS pieces of a row (and of the gain) per thread, all requested before the first is used: a row of up to 4096
+// elements is one round trip to memory for its workgroup.  Pieces past the row read its last one (not used).
+constexpr int ROW_CHUNKS = 2;
+__device__ __forceinline__ void load_row_chunks(const u16* x, const u16* g, int c0, int D, u32x4 (&v)[ROW_CHUNKS],
+                                                u32x4 (&gv)[ROW_CHUNKS]) {
+#pragma unroll
+    for (int u = 0; u < ROW_CHUNKS; ++u) {
+        if (c0 + 2048 * u >= D) break;                      // (uniform)
+        const int c = min(c0 + 2048 * u + (int)threadIdx.x * 8, D - 8);
+        v[u] = ldg16(x + c);
+        gv[u] = ldg16(g + c);
+    }
+}
+
 // The statistics loop of Example 3's first snapshot as a kernel of its own, with the gain:
 // Xg[i,:] = bf16( g * x ) and rstd[i] = rsqrt(mean(x^2) + eps); one workgroup per row, X read once.
 __global__ __launch_bounds__(256) void rms_gain_rows_kernel(const u16* X, const u16* g, u16* Xg, float* rstd, int D,
@@ -47,16 +61,22 @@ __global__ __launch_bounds__(256) void rms_gain_rows_kernel(const u16* X, const 
     const size_t row = blockIdx.x;
     const u16* x = X + row * D;
     float s = 0.f;
-    for (int c = threadIdx.x * 8; c < D; c += 256 * 8) {
-        const u32x4 v = ldg16(x + c), gv = ldg16(g + c);
-        u32x4 o;
+    for (int c0 = 0; c0 < D; c0 += ROW_CHUNKS * 2048) {
+        u32x4 v[ROW_CHUNKS], gv[ROW_CHUNKS];
+        load_row_chunks(x, g, c0, D, v, gv);
 #pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            const float a = bf_lo(v[q]), b = bf_hi(v[q]);
-            s += a * a + b * b;
-            o[q] = pack_bf16(bf_lo(gv[q]) * a, bf_hi(gv[q]) * b);
+        for (int u = 0; u < ROW_CHUNKS; ++u) {
+            const int c = c0 + 2048 * u + threadIdx.x * 8;
+            if (c >= D) break;
+            u32x4 o;
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                const float a = bf_lo(v[u][q]), b = bf_hi(v[u][q]);
+                s += a * a + b * b;
+                o[q] = pack_bf16(bf_lo(gv[u][q]) * a, bf_hi(gv[u][q]) * b);
+            }
+            *reinterpret_cast<u32x4*>(Xg + row * D + c) = o;
         }
-        *reinterpret_cast<u32x4*>(Xg + row * D + c) = o;
     }
     s = block_sum_256(s, red);
     if (threadIdx.x == 0) rstd[row] = rsqrtf(s / (float)D + eps);
@@ -111,26 +131,38 @@ __global__ __launch_bounds__(256) void ln_gain_rows_kernel(const u16* X, const u
     }
     const u16* x = X + row * D;
     float s = 0.f;
-    for (int c = threadIdx.x * 8; c < D; c += 256 * 8) {
-        const u32x4 v = ldg16(x + c), gv = ldg16(gamma + c);
-        u32x4 o;
+    u32x4 v[ROW_CHUNKS], gv[ROW_CHUNKS];
+    for (int c0 = 0; c0 < D; c0 += ROW_CHUNKS * 2048) {
+        load_row_chunks(x, gamma, c0, D, v, gv);
 #pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            const float a = bf_lo(v[q]), b = bf_hi(v[q]);
-            s += a + b;
-            o[q] = pack_bf16(bf_lo(gv[q]) * a, bf_hi(gv[q]) * b);
+        for (int u = 0; u < ROW_CHUNKS; ++u) {
+            const int c = c0 + 2048 * u + threadIdx.x * 8;
+            if (c >= D) break;
+            u32x4 o;
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                const float a = bf_lo(v[u][q]), b = bf_hi(v[u][q]);
+                s += a + b;
+                o[q] = pack_bf16(bf_lo(gv[u][q]) * a, bf_hi(gv[u][q]) * b);
+            }
+            *reinterpret_cast<u32x4*>(Xg + row * D + c) = o;
         }
-        *reinterpret_cast<u32x4*>(Xg + row * D + c) = o;
     }
     const float mu = block_sum_256(s, red) / (float)D;
     float s2 = 0.f;
-    for (int c = threadIdx.x * 8; c < D; c += 256 * 8) {
-        const u32x4 v = ldg16(x + c);
+    auto squares = [&](const u32x4& w) {
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
-            const float a = bf_lo(v[q]) - mu, b = bf_hi(v[q]) - mu;
+            const float a = bf_lo(w[q]) - mu, b = bf_hi(w[q]) - mu;
             s2 += a * a + b * b;
         }
+    };
+    if (D <= ROW_CHUNKS * 2048) {                  // the row is still in registers
+#pragma unroll
+        for (int u = 0; u < ROW_CHUNKS; ++u)
+            if (2048 * u + (int)threadIdx.x * 8 < D) squares(v[u]);
+    } else {
+        for (int c = threadIdx.x * 8; c < D; c += 256 * 8) squares(ldg16(x + c));
     }
     s2 = block_sum_256(s2, red);
     if (threadIdx.x == 0) {
