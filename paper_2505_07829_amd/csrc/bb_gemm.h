@@ -77,6 +77,7 @@
 namespace bb {
 
 enum { MODE_PLAIN = 0, MODE_GATEUP = 1, MODE_LN = 2, MODE_GATEUP_PRE = 3, MODE_LN_PRE = 4 };
+enum { PARTS_ONE = 0, PARTS_APART = 1, PARTS_FOLD = 2 };      // (see product_kernel)
 
 struct GemmArgs {
     const u16* A;        // [M, K]

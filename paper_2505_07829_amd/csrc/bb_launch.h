@@ -21,9 +21,9 @@ struct SliceArgs;
 template <int MODE, bool BT>
 void gemm_dispatch(int bm, bool full, bool odd, bool split, dim3 grid, hipStream_t st, const GemmArgs& a);
 
-// product_kernel<MODE, bm, bn, split, bt>: products without a norm prologue (bn = 128 and split: MODE_PLAIN)
+// product_kernel<MODE, bm, bn, parts, bt>: products without a norm prologue (bn = 128 and shares: MODE_PLAIN)
 template <int MODE, bool BT>
-void product_dispatch(int bm, int bn, bool split, dim3 grid, hipStream_t st, const GemmArgs& a);
+void product_dispatch(int bm, int bn, int parts, dim3 grid, hipStream_t st, const GemmArgs& a);
 
 // splitk_reduce_kernel<mode> (mode = MODE_PLAIN or MODE_GATEUP)
 void splitk_reduce_dispatch(int mode, const float* part, const float* ssqpart, unsigned short* C, int M, int N, int K,

@@ -1,6 +1,6 @@
 // Matrix products of many rows without a norm prologue: the main loop of the prefill programs.
 //
-//   MODE_PLAIN       C = A B [+ residual], or fp32 partial results of a share of the contraction (SPLIT)
+//   MODE_PLAIN       C = A B [+ residual], or fp32 partial results of a share of the contraction (PARTS_APART)
 //   MODE_GATEUP_PRE  H = SiLU(r A W1) (r A W3), A already carries the gain, r from its row kernel
 //   MODE_LN_PRE      C = r (A W - mu c) + b, A already carries gamma
 //
@@ -15,8 +15,11 @@
 // sides on one box; "cold": weights from memory, as a model's layers find them):
 //  - 16x16x32 matrix instructions: half the accumulator traffic per operation of the 32x32x16 form.  A loop of nothing
 //    else 1914 against 1760 TFLOP/s; 8192 x 4096 x 16384 869 -> 804.  Eight wavefronts, 2 x 4, 128 x 64 (64 x 64) each.
-//  - The XCDs start the contraction an eighth of it apart.  In step they all missed the memory-side cache on the same
-//    lines at the same time.  8192 x 4096 x 16384: 775 -> 727 (zeros: 720 -> 593); 4096 x 8192 x 2*28672 cold 2798 -> 2603.
+//  - The contraction runs from its first index to its last on every XCD, so that an element of C is the same sum whatever
+//    tile it lies in: equal rows give equal bits.  A 16x16x32 instruction adds to the bits of two 32x32x16 instructions over the
+//    same 32 indices, so the sums are gemm_kernel's too.  (Starting an eighth of the contraction apart per XCD spares the
+//    memory-side cache, on zeros 720 -> 593 at 8192 x 4096 x 16384, but made the order of a sum depend on the tile, and in the FFN
+//    of 4096 x 8192 x 28672 it is the slower one: 3796 against 3745 us.)
 //  - Where the weights that all XCDs read during one round of 256-row tiles fit the memory-side cache well (K <= 4096),
 //    groups of row tiles also start at different column tiles (p.rot): 8192 x 4096 x 16384 746 -> 732.  With longer
 //    contractions the other groups come too late: 4096 x 8192 x 2*28672 2540 -> 2810.
@@ -48,18 +51,22 @@ namespace bb {
 
 constexpr int PRODUCT_THREADS = 512;
 
-// SPLIT: p.nsplit workgroups per tile, each with p.nk_split steps (steps past the end of the contraction load zeros),
-// store fp32 partial results for splitk_reduce_kernel.
+// PARTS: how a contraction of several shares of p.nk_split steps each is summed (every share from zero, then the shares in
+// order): PARTS_ONE, there is one share; PARTS_APART, p.nsplit workgroups per tile, a share each (steps past the end of the
+// contraction load zeros), which store fp32 partial results for splitk_reduce_kernel; PARTS_FOLD, one workgroup, which adds
+// a finished share to a second set of accumulators: the same bits without partial results in memory.
 // BN: columns of a tile (of both weight matrices together): 256, or 128 with 128 rows: five stages of 32 KiB, half
 // the work per tile.  For products of so few tiles that a compute unit's loads are all that is in flight for it: cold, 128 x
 // 256 -> 128 x 128 tiles, 1000 x 7680 x 2880 92.9 -> 66.0 (96 and 184 tiles; transposed 100 -> 67), 300 x 4096 x 4096 48.6 -> 33.0,
 // 2048 x 8192 x 2048 90 -> 71; on a full chip they lose, 2048 x 11008 x 4096 148 -> 186.
 // RAGGED: the contraction's last step is incomplete (a multiple of 8): its loads take their whole offset per lane, and what lies
 // past the contraction gets one past the buffer, which loads zeros (A then row-major).
-template <int MODE, int BM, int BN, bool SPLIT, bool BT, bool RAGGED>
+template <int MODE, int BM, int BN, int PARTS, bool BT, bool RAGGED>
 __global__ __launch_bounds__(PRODUCT_THREADS) void product_kernel(const GemmArgs p) {
     static_assert(MODE == MODE_PLAIN || MODE == MODE_GATEUP_PRE || MODE == MODE_LN_PRE, "no norm prologue here");
-    static_assert(!SPLIT || MODE == MODE_PLAIN, "split contraction: plain products");
+    static_assert(PARTS == PARTS_ONE || MODE == MODE_PLAIN, "contraction in shares: plain products");
+    static_assert(PARTS != PARTS_FOLD || BN == 128, "shares added in registers: 128 x 128 tiles");
+    constexpr bool SPLIT = PARTS == PARTS_APART, FOLD = PARTS == PARTS_FOLD;
     static_assert((BN == 256 && (BM == 128 || BM == 256)) || (BN == 128 && BM == 128 && MODE == MODE_PLAIN), "tiles");
     constexpr bool DUAL = MODE == MODE_GATEUP_PRE;
     constexpr int WR = BM / 2;                        // rows of a wavefront (2 x 4 wavefronts, BN / 4 columns each)
@@ -130,9 +137,6 @@ __global__ __launch_bounds__(PRODUCT_THREADS) void product_kernel(const GemmArgs
             inB[q] = row < left;
         }
     }
-    // step kt of this workgroup as a step of the contraction, counted from an eighth of the share per XCD
-    const int skew = xcd * nk / 8;
-    auto kpos = [&](int kt) -> u32 { const int k = kt + skew; return (u32)(kt0 + (k >= nk ? k - nk : k)); };
     // The load-to-LDS instructions of step kt into the stage at LDS address dst.  Written in asm, because the compiler
     // makes every LDS read wait for every such transfer that it sees unless stages are arrays of their own and the loop is
     // unrolled over them.  They write no register; what orders them against the reads is the wait and the barrier of
@@ -150,11 +154,11 @@ __global__ __launch_bounds__(PRODUCT_THREADS) void product_kernel(const GemmArgs
                      ::"s"(__builtin_amdgcn_readfirstlane(dst)), "v"(voff), "s"(rs), "s"(there ? soff : 0u) : "m0");
     };
     auto dma_a = [&](int kt, u32 dst, int j) {
-        const u32 k = kpos(kt);
+        const u32 k = (u32)(kt0 + kt);
         to_lds(p.A, bytesA, k, lA[j], uA[j] + k * p.a_step, inA[j], dst + 1024u * (u32)(ADMA * w + j));
     };
     auto dma_b = [&](int kt, u32 dst, int x) {
-        const u32 k = kpos(kt);
+        const u32 k = (u32)(kt0 + kt);
         if (BT) {
             const bool second = DUAL && 8 * (BDMA * w + x) >= 128;
             to_lds(second ? p.B1 : p.B0, bytesB, k, lB[x], uB[x] + k * (2u * GEMM_BK), inB[x], dst + 1024u * (u32)(BDMA * w + x));
@@ -189,6 +193,25 @@ __global__ __launch_bounds__(PRODUCT_THREADS) void product_kernel(const GemmArgs
     for (int i = 0; i < MT; ++i)
 #pragma unroll
         for (int tt = 0; tt < NT; ++tt) acc[i][tt] = f32x4{0.f, 0.f, 0.f, 0.f};
+    f32x4 sum[FOLD ? MT : 1][FOLD ? NT : 1];          // FOLD: the finished shares
+    int until = p.nk_split;                           // and the steps until the next one is finished
+    if constexpr (FOLD) {
+#pragma unroll
+        for (int i = 0; i < MT; ++i)
+#pragma unroll
+            for (int tt = 0; tt < NT; ++tt) sum[i][tt] = f32x4{0.f, 0.f, 0.f, 0.f};
+    }
+    auto fold = [&]() {
+        if constexpr (FOLD) {
+#pragma unroll
+            for (int i = 0; i < MT; ++i)
+#pragma unroll
+                for (int tt = 0; tt < NT; ++tt) {
+                    sum[i][tt] += acc[i][tt];
+                    acc[i][tt] = f32x4{0.f, 0.f, 0.f, 0.f};
+                }
+        }
+    };
 
     Chunk fa[8], fb[2][NT];
     typedef __attribute__((address_space(3))) const char* lds_t;
@@ -270,6 +293,11 @@ __global__ __launch_bounds__(PRODUCT_THREADS) void product_kernel(const GemmArgs
         }
         curA = nxtA;
         curB = nxtB;
+        if (FOLD && --until == 0) {
+            fold();
+            until = p.nk_split;
+            __builtin_amdgcn_sched_barrier(0);
+        }
     };
 
     // the loads that stand before step 0: two tiles, or all but A of the last stage
@@ -307,6 +335,14 @@ __global__ __launch_bounds__(PRODUCT_THREADS) void product_kernel(const GemmArgs
         tail(kt, std::integral_constant<int, 2>());
         tail(kt, std::integral_constant<int, 3>());
         tail(kt, std::integral_constant<int, 4>());
+    }
+
+    // (a last share that is shorter, or nothing: the zeros change no sum, which begins at +0 and so is never -0)
+    if constexpr (FOLD) {
+#pragma unroll
+        for (int i = 0; i < MT; ++i)
+#pragma unroll
+            for (int tt = 0; tt < NT; ++tt) acc[i][tt] = sum[i][tt] + acc[i][tt];
     }
 
     // ---- epilogue: acc[i][tt][v] is row 16 i + l16 of the wavefront's rows, column 16 tt + 4 g + v of its columns

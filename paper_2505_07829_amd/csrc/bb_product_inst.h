@@ -7,15 +7,17 @@
 namespace bb {
 
 template <int MODE, bool BT>
-void product_dispatch(int bm, int bn, bool split, dim3 grid, hipStream_t st, const GemmArgs& a) {
+void product_dispatch(int bm, int bn, int parts, dim3 grid, hipStream_t st, const GemmArgs& a) {
     auto go = [&](auto kernel) { hipLaunchKernelGGL(kernel, grid, dim3(PRODUCT_THREADS), 0, st, a); };
     auto by_tile = [&](auto RAGGEDc) {
         constexpr bool R = decltype(RAGGEDc)::value;
-        if constexpr (MODE == MODE_PLAIN) {               // (split launches have 128-row tiles)
-            if (bn == 128) return split ? go(product_kernel<MODE, 128, 128, true, BT, R>) : go(product_kernel<MODE, 128, 128, false, BT, R>);
-            if (split) return go(product_kernel<MODE, 128, 256, true, BT, R>);
+        if constexpr (MODE == MODE_PLAIN) {
+            if (parts == PARTS_FOLD) return go(product_kernel<MODE, 128, 128, PARTS_FOLD, BT, R>);
+            if (parts == PARTS_APART)
+                return bm == 128 ? go(product_kernel<MODE, 128, 256, PARTS_APART, BT, R>) : go(product_kernel<MODE, 256, 256, PARTS_APART, BT, R>);
+            if (bn == 128) return go(product_kernel<MODE, 128, 128, PARTS_ONE, BT, R>);
         }
-        if (bm == 128) go(product_kernel<MODE, 128, 256, false, BT, R>); else go(product_kernel<MODE, 256, 256, false, BT, R>);
+        if (bm == 128) go(product_kernel<MODE, 128, 256, PARTS_ONE, BT, R>); else go(product_kernel<MODE, 256, 256, PARTS_ONE, BT, R>);
     };
     if (a.K % GEMM_BK) by_tile(std::true_type()); else by_tile(std::false_type());
 }

@@ -1,5 +1,5 @@
 // product_kernel instantiations: MODE_GATEUP_PRE, weights transposed ([N, K])
 #include "bb_product_inst.h"
 namespace bb {
-template void product_dispatch<MODE_GATEUP_PRE, true>(int, int, bool, dim3, hipStream_t, const GemmArgs&);
+template void product_dispatch<MODE_GATEUP_PRE, true>(int, int, int, dim3, hipStream_t, const GemmArgs&);
 }

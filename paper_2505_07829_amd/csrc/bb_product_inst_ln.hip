@@ -1,5 +1,5 @@
 // product_kernel instantiations: MODE_LN_PRE, weights row-major ([K, N])
 #include "bb_product_inst.h"
 namespace bb {
-template void product_dispatch<MODE_LN_PRE, false>(int, int, bool, dim3, hipStream_t, const GemmArgs&);
+template void product_dispatch<MODE_LN_PRE, false>(int, int, int, dim3, hipStream_t, const GemmArgs&);
 }
