@@ -137,7 +137,7 @@ def dominant_kernel(cfg, kernels):
 
 def variant_name(kernels):
     for kernel, name in (("ffn_stream", "stream"), ("ffn_nest", "nest"), ("few_gateup", "few-row"), ("few_ln", "few-row"),
-                         ("ffn_slices", "nest in parallel"), ("layernorm_rows", "normalised rows")):
+                         ("ffn_slices", "nest in parallel")):
         if kernel in kernels:
             return name
     return "prescale" if any(k.endswith("_prescaled") for k in kernels) else "snapshot1"

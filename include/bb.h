@@ -124,9 +124,9 @@ typedef enum bb_status {
  *                       where it is the faster one (D and F multiples of 64);
  *                       else SNAPSHOT1.  LN -> matmul: the few-row program up
  *                       to 254 rows for D >= 1536, and as far as it is the
- *                       faster one below (a rule on M, D and N); else
- *                       NORMALISED ROWS, but for D > 1024 with D N < 2^20,
- *                       which keeps PRESCALE.  Where the workspace has no room
+ *                       faster one below (a rule on M, D and N), else
+ *                       SNAPSHOT1 below 256 rows (D >= 1536: 255) and PRESCALE
+ *                       from there on.  Where the workspace has no room
  *                       for a program, the one that AUTO has without it:
  *                       for the few-row program STREAM for M <= 32, else
  *                       SNAPSHOT1 below 256 rows.
@@ -134,10 +134,6 @@ typedef enum bb_status {
  * The nest IN PARALLEL (AUTO only): a workgroup per 64 rows and 64 hidden
  * units keeps its slice of the hidden on chip and leaves fp32 partial outputs,
  * which a second launch adds in fixed order (the K-map of Example 3's epilogue).
- *
- * NORMALISED ROWS (AUTO only): the program of BB_VARIANT_UNFUSED, a row kernel
- * (two passes over the row) and a plain product, whose contraction may be split
- * over workgroups; no pass over W for gamma^T W and beta^T W.
  *
  * The FEW-ROW program (AUTO only) has PRESCALE's row kernel; then, per product,
  * one pass over the weights cut into equal shares for all compute units: fp32
@@ -204,10 +200,13 @@ int bb_rmsnorm_swiglu_ffn(const void* X, const void* g, const void* W1,
  * variance is the one-pass form sum(x^2)/D - mean^2 in fp32: rows whose
  * |mean|/std exceeds a few hundred lose accuracy.  BB_VARIANT_PRESCALE and the
  * few-row program take two passes over the row (mean, then the sum of squared
- * deviations) and have no such limit, nor have the normalised rows.  AUTO
- * runs SNAPSHOT1 only where the workspace has no room for the few-row
- * program; a caller with large means may select BB_VARIANT_PRESCALE or
- * BB_VARIANT_UNFUSED.  Workspace: bb_workspace_bytes(
+ * deviations) and have no such limit.  Which of them AUTO runs depends on the
+ * shape (see there; SNAPSHOT1 only below 256 rows, and with room for the
+ * few-row program only for D < 1536): a caller with large means
+ * selects BB_VARIANT_PRESCALE or BB_VARIANT_UNFUSED, which the transposed entry
+ * point does not have below 256 rows.  beta enters through beta^T W, summed in
+ * fp32 (the UNFUSED program alone rounds the normalised row with its beta to
+ * bf16).  Workspace: bb_workspace_bytes(
  * BB_OP_LAYERNORM_MATMUL, M, D, N) (fp32 column vectors of length N and their
  * partial sums).
  */
