@@ -28,7 +28,7 @@ if ROOT not in sys.path:
 PEAK_BF16_TFLOPS = 2500.0      # MI355X dense bf16 matrix peak
 PEAK_HBM_GBS = 8000.0          # MI355X HBM3E peak
 
-# HBM bytes per launch of the dominant kernel from rocprofv3 --pmc FETCH_SIZE / WRITE_SIZE runs of
+# HBM bytes per phase of the profile of the dominant kernel from rocprofv3 --pmc FETCH_SIZE / WRITE_SIZE runs of
 # this same script (profiles/hbm_traffic_c1_c2_c3_ffn.txt, attention: profiles/hbm_traffic_c2_c3_attention.txt) and of the
 # decode case in perf/cases.py (few_gateup: profiles/few_rows_and_grouped_attention_kernels.txt;
 # FETCH_SIZE scaled by 2.0, WRITE_SIZE by 1.0 as
@@ -38,7 +38,7 @@ TRAFFIC_SOURCE = ("carried from profiles/hbm_traffic_c1_c2_c3_ffn.txt, hbm_traff
                   "few_rows_and_grouped_attention_kernels.txt, products_and_parallel_nest_kernels.txt (rocprofv3 --pmc "
                   "FETCH_SIZE, WRITE_SIZE runs, scaled by a copy of known size); not measured in this run")
 MEASURED_TRAFFIC_BYTES = {
-    ("c1", "ffn_nest"): 2.2e6 + 0.7e6,          # (both launches of the nest in parallel)
+    ("c1", "ffn_slices"): 2.2e6 + 0.7e6,        # (the nest in parallel: both launches, as its phase is timed)
     ("c2", "ffn_stream"): 280.4e6 + 16.2e6,
     ("c2", "few_gateup"): 185.0e6 + 3.8e6,
     ("c2", "ffn_stream_t"): 275.0e6 + 0.7e6,
@@ -65,8 +65,8 @@ def roofline_block(kernel, bound, work, ms, traffic, step_work=None, step_ms=Non
     else:
         achieved, peak, unit, scale = work / (ms * 1e-3) / 1e9, PEAK_HBM_GBS, "GB/s", 1e9
     r = {"kernel": kernel, "bound": bound, "achieved": achieved, "peak": peak, "unit": unit, "frac": achieved / peak,
-         "traffic": traffic, "traffic_unit": "bytes per launch", "traffic_source": TRAFFIC_SOURCE if traffic else None,
-         "algorithmic": work, "algorithmic_unit": "flop per launch" if bound == "mfma" else "bytes per launch",
+         "traffic": traffic, "traffic_unit": "bytes per phase of the profile", "traffic_source": TRAFFIC_SOURCE if traffic else None,
+         "algorithmic": work, "algorithmic_unit": "flop per phase of the profile" if bound == "mfma" else "bytes per phase of the profile",
          "kernel_ms": ms}
     if step_work is not None:
         a = step_work / (step_ms * 1e-3) / scale
