@@ -28,7 +28,7 @@ if ROOT not in sys.path:
 PEAK_BF16_TFLOPS = 2500.0      # MI355X dense bf16 matrix peak
 PEAK_HBM_GBS = 8000.0          # MI355X HBM3E peak
 
-# HBM bytes per phase of the profile of the dominant kernel from rocprofv3 --pmc FETCH_SIZE / WRITE_SIZE runs of
+# HBM bytes per phase of the profile (a kernel and what adds its parts), dominant one, from rocprofv3 --pmc FETCH_SIZE / WRITE_SIZE runs of
 # this same script (profiles/hbm_traffic_c1_c2_c3_ffn.txt, attention: profiles/hbm_traffic_c2_c3_attention.txt) and of the
 # decode case in perf/cases.py (few_gateup: profiles/few_rows_and_grouped_attention_kernels.txt;
 # FETCH_SIZE scaled by 2.0, WRITE_SIZE by 1.0 as

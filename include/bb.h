@@ -359,7 +359,8 @@ size_t bb_attention_workspace_bytes(int64_t B, int64_t M, int64_t N, int64_t d,
  * bb_*_tune run every candidate program of the operator on the caller's
  * operands (same arguments as the operator): STREAM (FFN, M <= 32 only),
  * SNAPSHOT1, UNFUSED, PRESCALE (for the FFN M > 16 only), NEST (FFN, D <= 512)
- * and, where AUTO would run it, the few-row program; each once untimed and
+ * and, where AUTO would run it, the few-row program or the nest in parallel;
+ * each once untimed and
  * then `reps` (1..1000) times between two events on `stream`, which the call
  * waits for.  The fastest is recorded for exactly this (operator, M, D, F or N)
  * in a process-wide table that BB_VARIANT_AUTO consults, so later calls of
@@ -370,7 +371,9 @@ size_t bb_attention_workspace_bytes(int64_t B, int64_t M, int64_t N, int64_t d,
  *     no number of its own: where it wins, AUTO runs it and it reports as
  *     PRESCALE, whose row kernel it has, with its time in ms[PRESCALE]; where
  *     PRESCALE is no candidate, for the FFN up to 16 rows, `chosen` is the
- *     fastest of the others and only ms[0] shows its time.
+ *     fastest of the others and only ms[0] shows its time.  So it is with the
+ *     nest in parallel: AUTO runs it where it wins, `chosen` and ms[1..5] are
+ *     the variants that a caller can force, ms[0] shows its time.
  *   ms (host, 6 floats, may be NULL): ms[v] = mean milliseconds of variant v,
  *     -1 where v is not a candidate; ms[0] = the fastest.
  * A candidate that does not fit a caller-provided workspace is skipped.
