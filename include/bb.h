@@ -113,12 +113,14 @@ typedef enum bb_status {
  *                       alone: it wins where six pairs of wavefronts take all
  *                       hidden blocks at once).
  * BB_VARIANT_AUTO      the measured selection for exactly this shape if
- *                       bb_*_tune has recorded one, else, for the FFN: the
- *                       nest IN PARALLEL for D <= 256 and F <= 4096 while its
- *                       partial outputs stay below 28 MiB and, where NEST is
- *                       the alternative, its workgroups fit one round of the
- *                       compute units; NEST for D <= 256, F <= 768 and
- *                       M <= 4096; the few-row program up to 32 rows, and up
+ *                       bb_*_tune has recorded one, else, for the FFN: NEST
+ *                       for D <= 256, F <= 768 and M <= 4096, or, with memory
+ *                       of the caller (bb_rmsnorm_swiglu_ffn_partials) and
+ *                       where its workgroups fit one round of the compute
+ *                       units, the nest IN PARALLEL; that one beyond, for
+ *                       D <= 256 and F <= 4096 (transposed weights: from the
+ *                       smallest) while its partial outputs stay below 28 MiB;
+ *                       the few-row program up to 32 rows, and up
  *                       to 255 where it is the faster one (a rule on M, D and
  *                       F; D F >= 2^19); PRESCALE from 256 rows on and below
  *                       where it is the faster one (D and F multiples of 64);
@@ -134,6 +136,9 @@ typedef enum bb_status {
  * The nest IN PARALLEL (AUTO only): a workgroup per 64 rows and 64 hidden
  * units keeps its slice of the hidden on chip and leaves fp32 partial outputs,
  * which a second launch adds in fixed order (the K-map of Example 3's epilogue).
+ * The partial outputs lie in the workspace, but never where AUTO runs NEST
+ * without them: such a call touches no memory but its operands, so calls on
+ * several streams share nothing.
  *
  * The FEW-ROW program (AUTO only) has PRESCALE's row kernel; then, per product,
  * one pass over the weights cut into equal shares for all compute units: fp32
@@ -268,6 +273,24 @@ int bb_rmsnorm_swiglu_ffn_residual_t(const void* X, const void* g,
                                      const void* W2t, const void* R, void* Y,
                                      int64_t M, int64_t D, int64_t F, float eps,
                                      void* stream);
+
+/* ------------------------------------------------------------------------
+ * bb_rmsnorm_swiglu_ffn (R NULL) or bb_rmsnorm_swiglu_ffn_residual with memory
+ * of the caller for the partial outputs of the nest in parallel: `bytes` bytes
+ * of device memory at `partials`, 16-byte aligned, that overlap no operand and
+ * that nothing else uses until the call's kernels have run.  With at least
+ * bb_rmsnorm_swiglu_ffn_partials_bytes(M, D, F) of them AUTO runs that program
+ * in the place of NEST (64 x 256 x 704: 11 us in the place of 16.4); with
+ * fewer, with (NULL, 0), for other shapes (0 bytes) and with a forced variant the
+ * call is the one without.  Errors as there, and BB_ERR_WORKSPACE for NULL with
+ * bytes or a pointer without, BB_ERR_ALIGN, BB_ERR_ALIAS for the memory.
+ */
+size_t bb_rmsnorm_swiglu_ffn_partials_bytes(int64_t M, int64_t D, int64_t F);
+int bb_rmsnorm_swiglu_ffn_partials(const void* X, const void* g, const void* W1,
+                                   const void* W3, const void* W2, const void* R,
+                                   void* Y, int64_t M, int64_t D, int64_t F,
+                                   float eps, void* partials, size_t bytes,
+                                   void* stream);
 
 /* ------------------------------------------------------------------------
  * The UNFUSED block programs (Example 3 / Example 2, initial block programs):
@@ -431,7 +454,9 @@ int bb_shutdown(void);
  *   does the same on its first call on a device.  BB_OK, BB_ERR_ARCH, BB_ERR_HIP.
  * bb_rmsnorm_swiglu_ffn_static: bb_rmsnorm_swiglu_ffn (same arguments, same
  *   kernels, same variant choice, bit-identical output; a workspace without
- *   room for AUTO's few-row program makes that one, not this one, run another)
+ *   room for AUTO's few-row program makes that one, not this one, run another,
+ *   and the nest in parallel, which this one has room for, is what that one
+ *   runs with bb_rmsnorm_swiglu_ffn_partials)
  *   with its scratch (the
  *   hidden H, partial results of split contractions, the streaming kernels'
  *   partial sums and synchronisation words) in a static device array (96 MiB:

@@ -8,6 +8,7 @@ no fallback: if the library is missing or a call fails, an exception is raised.
 from __future__ import annotations
 
 import ctypes
+import functools
 import os
 from typing import Optional
 
@@ -34,11 +35,14 @@ EXPORTS = [
     "bb_calib_copy", "bb_calib_read", "bb_calib_mfma", "bb_calib_mfma_data",
     "bb_profile_enable", "bb_profile_count", "bb_profile_get", "bb_profile_calls", "bb_profile_count_of",
     "bb_profile_get_of", "bb_check_fault", "bb_debug_inject_fault", "bb_debug_set_spin_limit",
-    "bb_init", "bb_rmsnorm_swiglu_ffn_static",
+    "bb_init", "bb_rmsnorm_swiglu_ffn_static", "bb_rmsnorm_swiglu_ffn_partials", "bb_rmsnorm_swiglu_ffn_partials_bytes",
 ]
+
+_PARTIALS_MAX_D, _PARTIALS_MAX_F = 256, 768     # beyond, bb_rmsnorm_swiglu_ffn_partials_bytes is 0
 
 _lib = None
 _bf16 = None              # torch.bfloat16, once the library is loaded
+_OutOfMemory = MemoryError # torch's error for device memory, likewise
 _raw_stream = _device = None   # the current stream's handle of a device, the current device
 
 
@@ -60,7 +64,7 @@ def load() -> ctypes.CDLL:
     # both work in one device context; loaded the other way round the process ends up with two
     # runtimes and this library's sees no device.
     import torch
-    global _bf16, _raw_stream, _device
+    global _bf16, _raw_stream, _device, _OutOfMemory
     lib = ctypes.CDLL(LIB_PATH)
     vp, i64, f32, sz, ci = ctypes.c_void_p, ctypes.c_int64, ctypes.c_float, ctypes.c_size_t, ctypes.c_int
     lib.bb_rmsnorm_swiglu_ffn.argtypes = [vp, vp, vp, vp, vp, vp, i64, i64, i64, f32, vp]
@@ -79,6 +83,8 @@ def load() -> ctypes.CDLL:
     lib.bb_attention.argtypes = [vp, vp, vp, vp, i64, i64, i64, i64, i64, vp]
     lib.bb_attention_workspace_bytes.argtypes = [i64, i64, i64, i64, i64]
     lib.bb_attention_workspace_bytes.restype = sz
+    lib.bb_rmsnorm_swiglu_ffn_partials.argtypes = [vp, vp, vp, vp, vp, vp, vp, i64, i64, i64, f32, vp, sz, vp]
+    lib.bb_rmsnorm_swiglu_ffn_partials_bytes.argtypes, lib.bb_rmsnorm_swiglu_ffn_partials_bytes.restype = [i64, i64, i64], sz
     lib.bb_workspace_bytes.argtypes = [ci, i64, i64, i64]
     lib.bb_workspace_bytes.restype = sz
     lib.bb_set_workspace.argtypes = [vp, sz]
@@ -95,9 +101,11 @@ def load() -> ctypes.CDLL:
     lib.bb_profile_get_of.argtypes = [ci, ci, ctypes.POINTER(ctypes.c_float), ctypes.POINTER(ctypes.c_char_p)]
     for name in EXPORTS:
         fn = getattr(lib, name)
-        if name not in ("bb_workspace_bytes", "bb_status_string", "bb_attention_workspace_bytes"):
+        if name not in ("bb_workspace_bytes", "bb_status_string", "bb_attention_workspace_bytes",
+                        "bb_rmsnorm_swiglu_ffn_partials_bytes"):
             fn.restype = ci
     _bf16 = torch.bfloat16
+    _OutOfMemory = torch.cuda.OutOfMemoryError
     # (without a Stream object per call, where this torch offers the handle)
     _raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
     _device = getattr(torch._C, "_cuda_getDevice", None)
@@ -138,6 +146,25 @@ def _refuse(t, shape, name):
     raise ValueError(f"{name} has shape {tuple(t.shape)}, expected {tuple(shape)}")
 
 
+@functools.lru_cache(maxsize=1024)
+def _partials_bytes(M: int, D: int, F: int) -> int:
+    return load().bb_rmsnorm_swiglu_ffn_partials_bytes(M, D, F)     # (of the sizes alone)
+
+
+def _small_ffn(lib, X, g, W1, W3, W2, R, Y, M, D, F, eps) -> None:
+    """The FFN of a small model: with memory of this call for the partial outputs of the nest in parallel where AUTO takes
+    it.  The memory comes from torch's allocator, which orders its reuse on the current stream and keeps what a captured
+    graph uses; where there is none the call runs without."""
+    need, part = _partials_bytes(M, D, F), None
+    if need:
+        try:
+            part = X.new_empty(need // 2)         # (the cheapest way to that many bytes on X's device)
+        except _OutOfMemory:
+            need = 0
+    _check(lib.bb_rmsnorm_swiglu_ffn_partials(_ptr(X), _ptr(g), _ptr(W1), _ptr(W3), _ptr(W2), _ptr(R), _ptr(Y), M, D, F,
+                                              float(eps), _ptr(part), need, _stream()), "bb_rmsnorm_swiglu_ffn")
+
+
 def bb_rmsnorm_swiglu_ffn(X, g, W1, W3, W2, eps: float, Y=None, unfused: bool = False):
     """Y = (SiLU(Xh W1) * (Xh W3)) W2 with Xh = g * X / sqrt(mean(X^2) + eps).  Returns Y."""
     lib = load()
@@ -149,6 +176,9 @@ def bb_rmsnorm_swiglu_ffn(X, g, W1, W3, W2, eps: float, Y=None, unfused: bool = 
         import torch
         Y = torch.empty((M, D), dtype=torch.bfloat16, device=X.device)
     _require(Y, (M, D), "Y")
+    if D <= _PARTIALS_MAX_D and F <= _PARTIALS_MAX_F and not unfused:
+        _small_ffn(lib, X, g, W1, W3, W2, None, Y, M, D, F, eps)
+        return Y
     fn = lib.bb_rmsnorm_swiglu_ffn_unfused if unfused else lib.bb_rmsnorm_swiglu_ffn
     _check(fn(_ptr(X), _ptr(g), _ptr(W1), _ptr(W3), _ptr(W2), _ptr(Y), M, D, F, float(eps), _stream()),
            "bb_rmsnorm_swiglu_ffn" + ("_unfused" if unfused else ""))
@@ -202,6 +232,9 @@ def bb_rmsnorm_swiglu_ffn_residual(X, g, W1, W3, W2, R, eps: float, Y=None, tran
         import torch
         Y = torch.empty((M, D), dtype=torch.bfloat16, device=X.device)
     _require(Y, (M, D), "Y")
+    if D <= _PARTIALS_MAX_D and F <= _PARTIALS_MAX_F and not transposed:
+        _small_ffn(lib, X, g, W1, W3, W2, R, Y, M, D, F, eps)
+        return Y
     fn = lib.bb_rmsnorm_swiglu_ffn_residual_t if transposed else lib.bb_rmsnorm_swiglu_ffn_residual
     _check(fn(_ptr(X), _ptr(g), _ptr(W1), _ptr(W3), _ptr(W2), _ptr(R), _ptr(Y), M, D, F, float(eps), _stream()),
            "bb_rmsnorm_swiglu_ffn_residual")

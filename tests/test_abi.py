@@ -184,6 +184,25 @@ def test_workspace_of_few_rows_is_bounded(lib, op, M, D, FN):
     assert lib.bb_set_workspace(None, 0) == 0
 
 
+def test_partials_argument_errors(lib):
+    # operands of a 4 x 64 x 128 FFN at fake addresses, far apart
+    ops = [A * i for i in range(1, 6)]
+    call = lambda part, n, R=None, M=4, ops=ops, Y=7 * A: lib.bb_rmsnorm_swiglu_ffn_partials(
+        *ops, R, Y, M, 64, 128, 1e-6, part, n, None)
+    need = lib.bb_rmsnorm_swiglu_ffn_partials_bytes(4, 64, 128)
+    assert need == 2 * 4 * 64 * 4                            # an fp32 output for each 64 hidden units
+    assert call(8 * A + 8, need) == -3                       # misaligned
+    assert call(None, need) == -7 and call(8 * A, 0) == -7
+    for i in range(5):
+        assert call(ops[i], need) == -5                      # overlaps an operand
+    assert call(7 * A, need) == -5 and call(6 * A, need, R=6 * A) == -5
+    assert call(8 * A, need, M=0) == 0 and call(8 * A, need, M=-1) == -2
+    assert call(8 * A, need, Y=ops[0]) == -5 and call(8 * A, need, ops=[None] + ops[1:]) == -1
+    # nothing where AUTO has no use for it: wider models, more hidden units, more than one round of workgroups, bad sizes
+    for M, D, F in [(64, 264, 704), (64, 256, 776), (1473, 200, 696), (4112, 64, 128), (64, 7, 8), (0, 64, 64)]:
+        assert lib.bb_rmsnorm_swiglu_ffn_partials_bytes(M, D, F) == 0, (M, D, F)
+
+
 def test_calibration_argument_errors(lib):
     assert lib.bb_calib_copy(None, A, 1024, None) == -1
     assert lib.bb_calib_copy(A, 2 * A, 1000, None) == -3

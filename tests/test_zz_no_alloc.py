@@ -55,6 +55,12 @@ def test_two_calls_in_a_row_second_smaller_tiled_kernels(force):
     both((7, 512, 1408), 46)         # back to the streaming kernel: its zone was overwritten and is cleared again
 
 
+def test_two_calls_in_a_row_nest_in_parallel():
+    both((64, 256, 704), 51)         # partial outputs in the array
+    both((20, 128, 1032), 52)
+    both((1500, 200, 696), 53)       # the serial nest
+
+
 def test_two_calls_in_a_row_second_smaller_few_row_program():
     both((120, 1024, 2816), 48)      # hidden, partial sums and scaled rows in the array
     both((7, 512, 1408), 49)
