@@ -361,7 +361,9 @@ int bb_layernorm_matmul_unfused(const void* X, const void* gamma,
  * (this one with M = 1, or a BB_VARIANT_STREAM one) is replayed only while
  * no other entry point of the library, and no call that needs a larger
  * workspace, has run since its capture.  Any other captured launch may be
- * replayed among calls of every kind; the calls that rely on words of the
+ * replayed among calls of every kind, also after one that made the library's
+ * workspace larger: what a captured launch uses is kept until bb_shutdown or
+ * bb_set_workspace.  The calls that rely on words of the
  * workspace being in order clear them again once something that writes there
  * has been captured.  The environment variable BB_ATTN_WAVES=4|8 (read once) forces
  * the number of wavefronts per workgroup (32 queries each) instead of the
@@ -435,7 +437,8 @@ int bb_tune_clear(void);
  *   bb_rmsnorm_swiglu_ffn (default BB_VARIANT_AUTO, or the BB_VARIANT
  *   environment variable: "auto", "stream", "snapshot1", "unfused", "prescale");
  *   BB_VARIANT_UNFUSED also applies to bb_layernorm_matmul.
- * bb_shutdown: frees the library's own workspace (synchronises the device).
+ * bb_shutdown: frees the library's own workspace, and smaller ones kept for
+ *   captured launches (synchronises the device).
  */
 size_t bb_workspace_bytes(int op, int64_t M, int64_t D, int64_t F_or_N);
 int bb_set_workspace(void* dptr, size_t bytes);
