@@ -809,14 +809,34 @@ __global__ __launch_bounds__(256) void splitk_reduce_kernel(const float* part, c
     const int m = (int)(idx / groups), c0 = 8 * (int)(idx % groups);
     f32x4 a0 = {0, 0, 0, 0}, a1 = a0, b0 = a0, b1 = a0;
     float s2 = 0.f;
-    for (int sp = 0; sp < nsplit; ++sp) {
-        const float* src = part + ((size_t)sp * M + m) * ldp + c0;
-        a0 += *reinterpret_cast<const f32x4*>(src);
-        a1 += *reinterpret_cast<const f32x4*>(src + 4);
-        if (MODE == MODE_GATEUP) {
-            b0 += *reinterpret_cast<const f32x4*>(src + N);
-            b1 += *reinterpret_cast<const f32x4*>(src + N + 4);
-            s2 += ssqpart[(size_t)sp * M + m];
+    // (the loads of several parts before their additions, which keep their order: one part at a time waits a round trip to
+    // the memory-side cache for each)
+    constexpr int BATCH = MODE == MODE_GATEUP ? 4 : 8;
+    for (int sp = 0; sp < nsplit; sp += BATCH) {
+        f32x4 v[BATCH][MODE == MODE_GATEUP ? 4 : 2];
+        float q[BATCH];
+#pragma unroll
+        for (int j = 0; j < BATCH; ++j) {
+            const size_t row = (size_t)min(sp + j, nsplit - 1) * M + m;
+            const float* src = part + row * ldp + c0;
+            v[j][0] = *reinterpret_cast<const f32x4*>(src);
+            v[j][1] = *reinterpret_cast<const f32x4*>(src + 4);
+            if constexpr (MODE == MODE_GATEUP) {
+                v[j][2] = *reinterpret_cast<const f32x4*>(src + N);
+                v[j][3] = *reinterpret_cast<const f32x4*>(src + N + 4);
+                q[j] = ssqpart[row];
+            }
+        }
+#pragma unroll
+        for (int j = 0; j < BATCH; ++j) {
+            if (sp + j >= nsplit) break;
+            a0 += v[j][0];
+            a1 += v[j][1];
+            if constexpr (MODE == MODE_GATEUP) {
+                b0 += v[j][2];
+                b1 += v[j][3];
+                s2 += q[j];
+            }
         }
     }
     u32x4 o;

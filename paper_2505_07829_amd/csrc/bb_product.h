@@ -53,7 +53,7 @@ constexpr int PRODUCT_THREADS = 512;
 
 // PARTS: how a contraction of several shares of p.nk_split steps each is summed (every share from zero, then the shares in
 // order): PARTS_ONE, there is one share; PARTS_APART, p.nsplit workgroups per tile, a share each (steps past the end of the
-// contraction load zeros), which store fp32 partial results for splitk_reduce_kernel; PARTS_FOLD, one workgroup, which adds
+// contraction, and those that a share is shorter than the loop's stages, load zeros), which store fp32 partial results for splitk_reduce_kernel; PARTS_FOLD, one workgroup, which adds
 // a finished share to a second set of accumulators: the same bits without partial results in memory.
 // BN: columns of a tile (of both weight matrices together): 256, or 128 with 128 rows: five stages of 32 KiB, half
 // the work per tile.  For products of so few tiles that a compute unit's loads are all that is in flight for it: cold, 128 x
@@ -92,8 +92,9 @@ __global__ __launch_bounds__(PRODUCT_THREADS) void product_kernel(const GemmArgs
     const int rows_grp = min(p.group_m, p.tiles_m - grp * p.group_m);
     const int tm = grp * p.group_m + in_grp % rows_grp, tn = (in_grp / rows_grp + p.rot * grp) % p.tiles_n;
     const int nk_all = (p.K + GEMM_BK - 1) / GEMM_BK;
-    const int nk = SPLIT ? p.nk_split : nk_all;
+    const int nk = SPLIT ? max(p.nk_split, STAGES) : nk_all;
     const int kt0 = SPLIT ? split * p.nk_split : 0;
+    const int kend = SPLIT ? min(kt0 + p.nk_split, nk_all) : nk_all;
     const int m0 = tm * BM, n0 = tn * NCOL;
 
     const int lane = threadIdx.x & 63;
@@ -141,9 +142,10 @@ __global__ __launch_bounds__(PRODUCT_THREADS) void product_kernel(const GemmArgs
     // makes every LDS read wait for every such transfer that it sees unless stages are arrays of their own and the loop is
     // unrolled over them.  They write no register; what orders them against the reads is the wait and the barrier of
     // every step.  (One wait state between the scalar write of M0 and its use.)
-    // SPLIT: past the end of the contraction the buffer is empty and the load writes zeros.
+    // SPLIT: past the end of the share, or of the contraction, the buffer is empty and the load writes zeros (whose products
+    // change no sum).
     auto to_lds = [&](const u16* base, size_t bytes, u32 k, u32 voff, u32 soff, bool in, u32 dst) {
-        const bool there = !SPLIT || (int)k < nk_all;
+        const bool there = !SPLIT || (int)k < kend;
         if (RAGGED) {
             const bool last = (int)k == nk_all - 1;
             voff = !last ? voff : in ? voff + soff : 0xfffffff0u;

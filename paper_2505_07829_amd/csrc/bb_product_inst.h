@@ -13,6 +13,7 @@ void product_dispatch(int bm, int bn, int parts, dim3 grid, hipStream_t st, cons
         constexpr bool R = decltype(RAGGEDc)::value;
         if constexpr (MODE == MODE_PLAIN) {
             if (parts == PARTS_FOLD) return go(product_kernel<MODE, 128, 128, PARTS_FOLD, BT, R>);
+            if (parts == PARTS_APART && bn == 128) return go(product_kernel<MODE, 128, 128, PARTS_APART, BT, R>);
             if (parts == PARTS_APART)
                 return bm == 128 ? go(product_kernel<MODE, 128, 256, PARTS_APART, BT, R>) : go(product_kernel<MODE, 256, 256, PARTS_APART, BT, R>);
             if (bn == 128) return go(product_kernel<MODE, 128, 128, PARTS_ONE, BT, R>);
