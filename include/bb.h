@@ -118,7 +118,7 @@ typedef enum bb_status {
  *                       of the caller (bb_rmsnorm_swiglu_ffn_partials) and
  *                       where its workgroups fit one round of the compute
  *                       units, the nest IN PARALLEL; that one beyond, for
- *                       D <= 256 and F <= 4096 (transposed weights: from the
+ *                       D <= 256 and F <= 16384 (transposed weights: from the
  *                       smallest) while its partial outputs stay below 28 MiB;
  *                       the few-row program up to 32 rows, and up
  *                       to 255 where it is the faster one (a rule on M, D and
