@@ -1,7 +1,7 @@
 // Norm-prologue bf16 GEMM for gfx950, and what its relatives share.
 //
-// product_kernel (bb_product.h) runs the modes without a prologue (PLAIN, GATEUP_PRE, LN_PRE) wherever the contraction
-// consists of at least three complete steps; here they take ragged and shorter ones and operands of 4 GiB and more.
+// product_kernel (bb_product.h) runs the modes without a prologue (PLAIN, GATEUP_PRE, LN_PRE) on contractions of more than two
+// steps; here they take shorter ones and operands of 4 GiB and more.
 //
 // One kernel template covers the compute-bound block programs:
 //
@@ -197,8 +197,7 @@ __device__ __forceinline__ void quad_transpose_f32(float (&y)[4], bool upper, bo
 // SPLIT (PLAIN, GATEUP; for shapes with fewer tiles than half the compute
 // units, i.e. few rows): nsplit workgroups share a tile, each contracts
 // nk_split steps of the contraction range (steps past the end load zeros, so
-// SPLIT kernels are built with FULL = false unless the steps divide evenly
-// among the workgroups) and stores its fp32 accumulators
+// SPLIT kernels are built with FULL = false) and stores its fp32 accumulators
 // (GATEUP: and its partial row sums of squares) instead of running the
 // epilogue; splitk_reduce_kernel adds the partial results in fixed order and
 // applies the epilogue.  This is Rule 3's parallel reduction over the

@@ -21,6 +21,7 @@ void gemm_dispatch(int bm, bool full, bool odd, bool split, dim3 grid, hipStream
     // each), so that no A fragment is prepared twice (kernel traces: c3's gate/up with the statistics in the loop
     // 362 -> 336 us, c5's LN product 1035-1100 -> 991 us).  Transposed weights: c3's gate/up 295 -> 287 us, c5's
     // product 861 -> 827 us (relative to the row-major kernels of the same runs).
+    // (The modes without a prologue come here with contractions of one or two steps and with operands of 4 GiB and more only.)
     auto go = [&](auto BMc, auto FULLc, auto ODDc, auto SPLITc) {
         constexpr int BM = decltype(BMc)::value;
         constexpr bool FULL = decltype(FULLc)::value;
@@ -35,11 +36,7 @@ void gemm_dispatch(int bm, bool full, bool odd, bool split, dim3 grid, hipStream
     using B256 = std::integral_constant<int, 256>;
     if (split) {
         if constexpr (MODE == MODE_PLAIN || MODE == MODE_GATEUP) {
-            if (bm == 256) {
-                if constexpr (MODE == MODE_PLAIN) by_odd(B256(), F_(), T());
-            } else {
-                by_odd(B128(), F_(), T());
-            }
+            by_odd(B128(), F_(), T());
         }
         return;
     }

@@ -17,7 +17,7 @@ struct FewArgs;
 struct SliceArgs;
 
 // gemm_kernel<MODE, bm, full, odd, split, bt> on `grid` workgroups (defined per MODE and per weight
-// layout in bb_gemm_inst_*.hip); split launches exist for MODE_PLAIN and MODE_GATEUP only
+// layout in bb_gemm_inst_*.hip); split launches exist for MODE_PLAIN and MODE_GATEUP only, with bm = 128
 template <int MODE, bool BT>
 void gemm_dispatch(int bm, bool full, bool odd, bool split, dim3 grid, hipStream_t st, const GemmArgs& a);
 
