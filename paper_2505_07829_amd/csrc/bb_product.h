@@ -21,8 +21,8 @@
 //    memory-side cache, on zeros 720 -> 593 at 8192 x 4096 x 16384, but made the order of a sum depend on the tile, and in the FFN
 //    of 4096 x 8192 x 28672 it is the slower one: 3796 against 3745 us.)
 //  - Where the weights that all XCDs read during one round of 256-row tiles fit the memory-side cache well (K <= 4096),
-//    groups of row tiles also start at different column tiles (p.rot): 8192 x 4096 x 16384 746 -> 732.  With longer
-//    contractions the other groups come too late: 4096 x 8192 x 2*28672 2540 -> 2810.
+//    groups of row tiles also start at different column tiles (p.rot): LN of 8192 x 4096 x 16384 823 -> 812.  With longer
+//    contractions the other groups come too late: FFN of 4096 x 8192 x 28672 3797 -> 3915.
 //  - Three stages of the weights, which come from memory (64 contraction indices each), and with 128-row tiles of A;
 //    with 256-row tiles two stages of A fill the 160 KiB.  256-row tiles, two -> three stages of the weights, cold:
 //    2048 x 4096 x 2*11008 284 -> 275, 4096 x 28672 x 8192 1370 -> 1278 (weights transposed 1562 -> 1367); 128-row tiles,
@@ -33,8 +33,8 @@
 //    gains nothing: they come back in order with the loads behind them.
 //  - A in panels of 64 columns ([K / 64][M][64], written so by the kernel before): a tile is 32 KiB in one piece instead
 //    of 256 pieces a row apart.  4096 x 28672 x 8192 (rows 57 KB apart) 1466 -> 1365; rows of 8 KB: equal.
-// Together against the 32x32x16 loop of gemm_kernel, cold: 2048 x 4096 x 2*11008 294 -> 275, 8192 x 4096 x 16384 833 ->
-// 745, 4096 x 8192 x 2*28672 2809 -> 2615, 4096 x 28672 x 8192 1505 -> 1286.
+// Together against the 32x32x16 loop of gemm_kernel, cold: 2048 x 4096 x 2*11008 294 -> 280, 8192 x 4096 x 16384 (LN) 833 ->
+// 796, 4096 x 8192 x 2*28672 2809 -> 2588, 4096 x 28672 x 8192 1505 -> 1268.
 //
 // LDS: rows of 128 bytes (A, transposed weights) with the chunk index XOR row / 2 % 8 (lds_pos); row-major weights as
 // they lie in memory, chunk index XOR 2 (row % 4 + 4 (row / 8 % 2)): the 32 lanes of one pass of a transposing read
