@@ -179,7 +179,7 @@ typedef enum bb_op {
  * (Rule 4).  M may be any value >= 0 (M == 0 returns BB_OK and launches
  * nothing); D and F must be positive multiples of 8.
  * Needs a workspace of bb_workspace_bytes(BB_OP_RMSNORM_SWIGLU_FFN, M, D, F)
- * bytes: taken from bb_set_workspace() if one is set, otherwise allocated by
+ * bytes (a call that runs NEST none): taken from bb_set_workspace() if one is set, otherwise allocated by
  * the library on first use (that call may synchronise the device) and cached.
  * Two calls that share the workspace must not overlap in time.
  */
@@ -422,10 +422,12 @@ int bb_tune_clear(void);
  *
  * bb_workspace_bytes: bytes of device scratch `op` needs for the given sizes
  *   (third size is F for the FFN ops, N for the LN ops); the maximum over
- *   STREAM, SNAPSHOT1, PRESCALE and AUTO's few-row program, the last left out
- *   where it alone would take the FFN beyond BB_STATIC_SCRATCH_BYTES (96 MiB
- *   have room for it there; with less AUTO runs the tiled programs).  The
- *   UNFUSED candidate needs
+ *   STREAM, SNAPSHOT1, PRESCALE, AUTO's few-row program and, for the FFN, the
+ *   nest in parallel (its partial outputs, also where only the transposed
+ *   layout or bb_*_tune puts them there), the last two left out where they
+ *   alone would take the FFN beyond BB_STATIC_SCRATCH_BYTES (96 MiB have room
+ *   for them there; with less AUTO runs the other programs).  The UNFUSED
+ *   candidate needs
  *   bb_workspace_bytes(BB_OP_*_UNFUSED, ...): a caller who provides the
  *   workspace and wants it considered by bb_*_tune sizes for the larger of the
  *   two.  Returns 0 for invalid sizes.
