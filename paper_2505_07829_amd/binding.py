@@ -154,7 +154,8 @@ def _partials_bytes(M: int, D: int, F: int) -> int:
 def _small_ffn(lib, X, g, W1, W3, W2, R, Y, M, D, F, eps) -> None:
     """The FFN of a small model: with memory of this call for the partial outputs of the nest in parallel where AUTO takes
     it.  The memory comes from torch's allocator, which orders its reuse on the current stream and keeps what a captured
-    graph uses; where there is none the call runs without."""
+    graph uses (torch.cuda.graph: a capture that torch does not know of needs the C entry point, with memory of its own); where
+    there is none the call runs without."""
     need, part = _partials_bytes(M, D, F), None
     if need:
         try:
