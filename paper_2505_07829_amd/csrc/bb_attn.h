@@ -145,7 +145,13 @@ __device__ __forceinline__ void attention_combine_row(const float* part, const f
 // parallel form); each stores its accumulators as significand-exponent pairs
 // (output sums and row sum at its own row exponents) and
 // attention_combine_kernel adds them the Appendix's way.
-template <int DK, int DV, int TAIL, int NW, bool KSPLIT = false>
+// FLAT: K and V by global load-to-LDS, fragments read two matrix instructions ahead; else by buffer loads and three ahead.  The
+// global form belongs to the FLAT family: next to it every wait for an LDS read is a wait for all of them, which costs where a
+// compute unit has one workgroup of four wavefronts, and is the faster one where two share it and fill each other's waits (see
+// attn_flat_wins).  The same bits.  Buffer loads, us, problems x queries x keys, before -> now: 8 x 1000 x 3000 48.5 -> 45.2, 16 x
+// 2048 x 8192 142 -> 133, 7 x 2757 x 4236 67.7 -> 63.4, 32 x 4096 x 4096 (eight wavefronts) 241.5 -> 240.3, 24 x 3000 x 5000 with
+// d 64 179.7 -> 170.5.
+template <int DK, int DV, int TAIL, int NW, bool KSPLIT = false, bool FLAT = false>
 __global__ __launch_bounds__(64 * NW, 2) void attention_kernel(const AttnArgs p) {
     constexpr int ATTN_BQ = 32 * NW;
     constexpr int CK = DK / 8, CV = DV / 8;          // 16-byte chunks per K / V row
@@ -203,8 +209,6 @@ __global__ __launch_bounds__(64 * NW, 2) void attention_kernel(const AttnArgs p)
         rowVd[j] = row;
         offVd[j] = (u32)(row * DV + 8 * chunk);
     }
-    // (buffer loads: next to the FLAT form every wait for an LDS read is a wait for all of them.  8 x 1000 x 3000 keys 48.8 ->
-    // 45.2 us, 32 x 4096 x 4096 243.5 -> 241.2, with fragments read three instead of two instructions ahead)
     const rsrc_t rsK = make_rsrc(Kb, (size_t)nkeys * DK * 2), rsV = make_rsrc(Vb, (size_t)nkeys * DV * 2);
     // which: 0 nothing, 1 a complete block, 2 the last block
     auto dma_k = [&](int kt, u32x4* dK, auto WHICH) {
@@ -215,7 +219,8 @@ __global__ __launch_bounds__(64 * NW, 2) void attention_kernel(const AttnArgs p)
 #pragma unroll
         for (int j = 0; j < NIK; ++j) {
             const u32 off = W == 2 ? offKd[j] - (u32)(max(rowKd[j] - rmax, 0) * DK) : offKd[j];
-            (KSPLIT ? buffer_to_lds16_nt : buffer_to_lds16)(rsK, 2 * off, (u32)(key0 * DK) * 2u, dK + (NIK * w + j) * 64);
+            if (FLAT) (KSPLIT ? load_to_lds16_nt : load_to_lds16)(reinterpret_cast<const char*>(Kb) + (u32)(2 * (off + (u32)(key0 * DK))), dK + (NIK * w + j) * 64);
+            else (KSPLIT ? buffer_to_lds16_nt : buffer_to_lds16)(rsK, 2 * off, (u32)(key0 * DK) * 2u, dK + (NIK * w + j) * 64);
         }
     };
     auto dma_v = [&](int kt, u32x4* dV, auto WHICH) {
@@ -226,7 +231,8 @@ __global__ __launch_bounds__(64 * NW, 2) void attention_kernel(const AttnArgs p)
 #pragma unroll
         for (int j = 0; j < NIV; ++j) {
             const u32 off = W == 2 ? offVd[j] - (u32)(max(rowVd[j] - rmax, 0) * DV) : offVd[j];
-            (KSPLIT ? buffer_to_lds16_nt : buffer_to_lds16)(rsV, 2 * off, (u32)(key0 * DV) * 2u, dV + (NIV * w + j) * 64);
+            if (FLAT) (KSPLIT ? load_to_lds16_nt : load_to_lds16)(reinterpret_cast<const char*>(Vb) + (u32)(2 * (off + (u32)(key0 * DV))), dV + (NIV * w + j) * 64);
+            else (KSPLIT ? buffer_to_lds16_nt : buffer_to_lds16)(rsV, 2 * off, (u32)(key0 * DV) * 2u, dV + (NIV * w + j) * 64);
         }
     };
 
@@ -263,7 +269,7 @@ __global__ __launch_bounds__(64 * NW, 2) void attention_kernel(const AttnArgs p)
     using I1 = std::integral_constant<int, 1>;
     using I2 = std::integral_constant<int, 2>;
     constexpr int NS = 2 * NKS, NPV = 4 * NDS;        // matrix instructions of the two products
-    constexpr int PDK = 3, PDV = 3;                   // fragment reads run this many matrix instructions ahead
+    constexpr int PDK = FLAT ? 2 : 3, PDV = PDK;      // fragment reads run this many matrix instructions ahead
 
     f32x16 sc[2][2];                                  // scores of the blocks of even / odd index, two 32-key subtiles each
     float mloc = -INFINITY;                           // maximum of the block whose scores were computed last

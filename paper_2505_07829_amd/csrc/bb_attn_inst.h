@@ -10,27 +10,35 @@
 namespace bb {
 
 // tail: iterations left after the two-per-trip main loop (1..4); nw: wavefronts per workgroup (4 or 8);
-// ksplit > 1: keys split over ksplit workgroups per (problem, query block), then the combine kernel
+// ksplit > 1: keys split over ksplit workgroups per (problem, query block), then the combine kernel; flat (four wavefronts, d =
+// dv = 128, tail 3 or 4): the FLAT kernels
 template <int DK, int DV>
-void attn_tiled_launch(int tail, int nw, int ksplit, dim3 grid, dim3 block, hipStream_t st, const AttnArgs& a) {
-    auto go_nw = [&](auto NWC) {
+void attn_tiled_launch(int tail, int nw, int ksplit, bool flat, dim3 grid, dim3 block, hipStream_t st, const AttnArgs& a) {
+    using T = std::true_type;
+    using F_ = std::false_type;
+    auto go = [&](auto NWC, auto KSPLITC, auto FLATC) {
         constexpr int NW = decltype(NWC)::value;
-        if (tail == 1) hipLaunchKernelGGL((attention_kernel<DK, DV, 1, NW>), grid, block, 0, st, a);
-        else if (tail == 2) hipLaunchKernelGGL((attention_kernel<DK, DV, 2, NW>), grid, block, 0, st, a);
-        else if (tail == 3) hipLaunchKernelGGL((attention_kernel<DK, DV, 3, NW>), grid, block, 0, st, a);
-        else hipLaunchKernelGGL((attention_kernel<DK, DV, 4, NW>), grid, block, 0, st, a);
+        constexpr bool KS = decltype(KSPLITC)::value, FL = decltype(FLATC)::value;
+        if (!FL && tail == 1) hipLaunchKernelGGL((attention_kernel<DK, DV, 1, NW, KS>), grid, block, 0, st, a);
+        else if (!FL && tail == 2) hipLaunchKernelGGL((attention_kernel<DK, DV, 2, NW, KS>), grid, block, 0, st, a);
+        else if (tail == 3) hipLaunchKernelGGL((attention_kernel<DK, DV, 3, NW, KS, FL>), grid, block, 0, st, a);
+        else hipLaunchKernelGGL((attention_kernel<DK, DV, 4, NW, KS, FL>), grid, block, 0, st, a);
+    };
+    auto four = [&](auto KSPLITC) {
+        using W4 = std::integral_constant<int, 4>;
+        if constexpr (DK == 128 && DV == 128) {
+            if (flat) return go(W4(), KSPLITC, T());
+        }
+        go(W4(), KSPLITC, F_());
     };
     if (ksplit > 1) {
-        if (tail == 1) hipLaunchKernelGGL((attention_kernel<DK, DV, 1, 4, true>), grid, block, 0, st, a);
-        else if (tail == 2) hipLaunchKernelGGL((attention_kernel<DK, DV, 2, 4, true>), grid, block, 0, st, a);
-        else if (tail == 3) hipLaunchKernelGGL((attention_kernel<DK, DV, 3, 4, true>), grid, block, 0, st, a);
-        else hipLaunchKernelGGL((attention_kernel<DK, DV, 4, 4, true>), grid, block, 0, st, a);
+        four(T());
         hipLaunchKernelGGL((attention_combine_kernel<DV>), dim3((unsigned)((size_t)a.B * a.M)), dim3(64), 0, st,
                            (const float*)a.part, (const float*)a.ml, a.O, ksplit, a.c);
     } else if (nw == 8) {
-        go_nw(std::integral_constant<int, 8>{});
+        go(std::integral_constant<int, 8>(), F_(), F_());
     } else {
-        go_nw(std::integral_constant<int, 4>{});
+        four(F_());
     }
 }
 

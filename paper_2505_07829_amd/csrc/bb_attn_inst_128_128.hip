@@ -1,7 +1,7 @@
 // attention kernel instantiations: head dimensions d = 128, dv = 128
 #include "bb_attn_inst.h"
 namespace bb {
-template void attn_tiled_launch<128, 128>(int, int, int, dim3, dim3, hipStream_t, const AttnArgs&);
+template void attn_tiled_launch<128, 128>(int, int, int, bool, dim3, dim3, hipStream_t, const AttnArgs&);
 template void attn_decode_launch<128, 128>(dim3, hipStream_t, const AttnArgs&);
 template void attn_group_launch<128, 128>(int, dim3, hipStream_t, const AttnArgs&);
 }

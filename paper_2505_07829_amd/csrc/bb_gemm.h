@@ -131,6 +131,10 @@ constexpr int vmcnt_imm(int n) { return 0x0F70 | (n & 15) | ((n >> 4) << 14); }
 __device__ __forceinline__ void load_to_lds16(const void* src, void* dst) {
     __builtin_amdgcn_global_load_lds((gptr_t)src, (lptr_t)dst, 16, 0, 0);
 }
+// the same with the non-temporal cache policy (data that is read once)
+__device__ __forceinline__ void load_to_lds16_nt(const void* src, void* dst) {
+    __builtin_amdgcn_global_load_lds((gptr_t)src, (lptr_t)dst, 16, 0, 2);
+}
 
 // The same through a buffer resource (base address and size in four scalar registers): lane i copies the 16
 // bytes at base + voff (per lane) + soff (wavefront-uniform, a scalar register) to LDS address dst + 16 i.  The

@@ -52,7 +52,7 @@ void slice_launch(bool bt, hipStream_t st, const SliceArgs& a, unsigned short* Y
 // attention: tiled kernel (ksplit > 1: split keys + combine kernel), one-query and few-query streaming kernels
 // (defined per pair of head dimensions in bb_attn_inst_*.hip)
 template <int DK, int DV>
-void attn_tiled_launch(int tail, int nw, int ksplit, dim3 grid, dim3 block, hipStream_t st, const AttnArgs& a);
+void attn_tiled_launch(int tail, int nw, int ksplit, bool flat, dim3 grid, dim3 block, hipStream_t st, const AttnArgs& a);
 template <int DK, int DV>
 void attn_decode_launch(dim3 grid, hipStream_t st, const AttnArgs& a);
 template <int DK, int DV>       // mt = 1 or 2 groups of 16 queries

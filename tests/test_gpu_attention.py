@@ -151,6 +151,23 @@ def test_eight_wavefront_workgroups_on_the_shape_that_selects_them():
 
 
 # ---------------------------------------------------------------- few queries: keys split over workgroups
+# More workgroups of four wavefronts than compute units: the kernels with global loads, of each number of iterations behind the
+# main loop, complete and ragged last key blocks; the shortest loops taken (8, 10 and 12 blocks).  The same bits as of fewer
+# problems, which the kernels with buffer loads take (as many shares of the keys: 64 x 4 workgroups of 19 blocks each).
+@pytest.mark.parametrize("B,M,N,fewer", [(20, 1664, 1000, 10), (20, 1664, 820, 10), (20, 1640, 768, 10), (20, 1664, 705, 10),
+                                         (5, 1957, 4862, 4), (5, 1957, 4864, 4), (8, 1024, 4001, None), (12, 1200, 2560, None),
+                                         (7, 1957, 4300, None)])
+def test_workgroups_that_share_compute_units(B, M, N, fewer):
+    Q, K, V = (t.cuda() for t in bb_inputs.make_attn(B, M, N, 128, 128, seed=B + M + N))
+    O = bb.bb_attention(Q, K, V)
+    if fewer is not None:
+        for b0 in (0, B - fewer):
+            part = bb.bb_attention(*[t[b0:b0 + fewer].contiguous() for t in (Q, K, V)])
+            assert torch.equal(O[b0:b0 + fewer].view(torch.int16), part.view(torch.int16))
+    rows = [0, M - 1, M, B * M - 1] + list(range(57, B * M, 499))
+    assert rel_err(O.reshape(-1, 128)[rows], orc.attention(Q.cpu(), K.cpu(), V.cpu(), rows=rows)) <= TOL
+
+
 @pytest.mark.parametrize("B,M,N", [(32, 1, 4096), (8, 1, 8192), (4, 16, 2048), (2, 130, 4096), (1, 1, 777),
                                    (3, 5, 64 * 13), (16, 1, 4096 + 17), (3, 1, 1), (2, 1, 63), (5, 1, 257),
                                    (1, 1, 70000), (600, 1, 1100), (2, 2, 8192)])
